@@ -326,7 +326,8 @@ struct GridLayout {
         o_iperm = o_perm + align256(sizeof(int) * (size_t)n_src);
         o_spts = o_iperm + align256(sizeof(int) * (size_t)n_src);
         o_s32 = o_spts + align256(sizeof(double) * (size_t)n_src * padded_dim(dim));
-        o_bvh = o_s32 + align256(sizeof(float) * 2 * (size_t)n_src * dim);   // FP32 + fixed-point
+        // FP32 + fixed-point
+        o_bvh = o_s32 + align256(sizeof(float) * (2 * (size_t)n_src * dim + kPad32));
         bytes = o_bvh + (lbvh ? bvh_node_bytes(n_src, dim) : 0);
     }
     // Points g's arrays into the block at base.
@@ -542,7 +543,7 @@ static pcms_status grid_create(int64_t n_src, int32_t dim, const double *inv_sca
         (e = hipMalloc(&g->perm, sizeof(int) * (size_t)n_src)) != hipSuccess ||
         (e = hipMalloc(&g->iperm, sizeof(int) * (size_t)n_src)) != hipSuccess ||
         (e = hipMalloc(&g->spts, sizeof(double) * (size_t)n_src * padded_dim(dim))) != hipSuccess ||
-        (e = hipMalloc(&g->spts32, sizeof(float) * 2 * (size_t)n_src * dim)) != hipSuccess ||
+        (e = hipMalloc(&g->spts32, sizeof(float) * (2 * (size_t)n_src * dim + kPad32))) != hipSuccess ||
         (lbvh && (e = hipMalloc(&g->bvh_nodes, bvh_node_bytes(n_src, dim))) != hipSuccess)) {
         grid_alloc_free(g);
         return hip_fail(e, "hipMalloc(grid)");
@@ -936,7 +937,7 @@ pcms_status pcms_batch_plan_create(const pcms_problem *problems, int32_t n,
         B.nf = P.n_fields;
         B.nfs = padded_dim(P.n_fields);
         B.k_cap = P.k_cap;
-        B.words = target_words(P.radius.mode, P.radius.k, P.k_cap);
+        B.words = target_words(P.radius.mode, P.radius.k, P.k_cap, P.dim);
         B.stride = B.words | 1;
         B.mode = P.radius.mode;
         B.k = P.radius.k;

@@ -256,24 +256,32 @@ struct BoxTest32 {
     }
 };
 
-// Calls leaf(beg, end) for the sorted-source ranges of the leaves whose box
-// is within reach of the ball D < rho2 around t (a superset of the sources
-// inside it), in ascending order.  Records are read as 16-byte vectors (the
-// stride is a multiple of four floats on 256-byte aligned storage) and
-// tested in FP32 (BoxTest32).
-template <int D, bool UNIT, class L>
-PCMS_HD PCMS_INLINE void bvh_leaves(const GridParams &gp, const BvhView &bv, const double (&t)[D],
-                                    double rho2, L &&leaf)
-{
-    constexpr int S = bvh_stride(D);
-    const BoxTest32<D, UNIT> within(gp, t, rho2);
-    int r = 0;
-    while (r >= 0) {
+// The sorted-source ranges of the leaves whose box is within reach of the
+// ball D < rho2 around t (a superset of the sources inside it), in ascending
+// order.  Records are read as 16-byte vectors (the stride is a multiple of
+// four floats on 256-byte aligned storage) and tested in FP32 (BoxTest32).
+template <int D, bool UNIT>
+struct BvhIter {
+    const float *__restrict__ nodes;
+    BoxTest32<D, UNIT> within;
+    int r;
+    PCMS_HD PCMS_INLINE BvhIter(const GridParams &gp, const BvhView &bv, const double (&t)[D],
+                                double rho2)
+        : nodes(bv.nodes), within(gp, t, rho2), r(0)
+    {
+    }
+    // Visits one record: a leaf's range if it is one within reach, else an
+    // empty one; false after the last.
+    PCMS_HD PCMS_INLINE bool next(int &beg, int &end)
+    {
+        constexpr int S = bvh_stride(D);
+        beg = end = 0;
+        if (r < 0) return false;
 #ifdef PCMS_HOST_EMULATION
         ++pcms_emu_nodes;
 #endif
         float rec[S];
-        const float4 *q = reinterpret_cast<const float4 *>(bv.nodes + (size_t)r * S);
+        const float4 *q = reinterpret_cast<const float4 *>(nodes + (size_t)r * S);
 #pragma unroll
         for (int j = 0; j < S / 4; ++j) {
             const float4 v = q[j];
@@ -284,14 +292,14 @@ PCMS_HD PCMS_INLINE void bvh_leaves(const GridParams &gp, const BvhView &bv, con
         }
         const bool hit = within(rec);
         const int c0 = bvh_int(rec, 2 * D), rope = bvh_int(rec, 2 * D + 1);
-        if (c0 < 0) {
-            if (hit) leaf(bvh_int(rec, 2 * D + 2), bvh_int(rec, 2 * D + 3));
-            r = rope;
-        } else {
-            r = hit ? c0 : rope;
+        r = c0 < 0 || !hit ? rope : c0;
+        if (hit && c0 < 0) {
+            beg = bvh_int(rec, 2 * D + 2);
+            end = bvh_int(rec, 2 * D + 3);
         }
+        return true;
     }
-}
+};
 
 // Radius of a ball expected to hold k sources: the distance from t to the
 // box of the smallest subtree on the way to t (descending toward the child

@@ -83,6 +83,7 @@ struct GridParams {
     double g[kMaxDim];      // metric factors
     double qs[kMaxDim];     // quantum of the 32-bit source records (a power of two)
     double iqs[kMaxDim];    // 1 / qs
+    double wm;              // metric bucket width (of dimension 0: wm / sub)
     double density;         // sources per unit metric volume of the bounding box
 };
 
@@ -158,7 +159,7 @@ PCMS_HD inline void grid_params_compute(const double *lo, const double *hi, int 
             const double wk = k == 0 ? wm / p.sub : wm;
             if (ext[k] > 0.0) {
                 double nk = floor(ext[k] / wk) + 1.0;
-                nk = fmin(nk, 1073741824.0);
+                nk = fmin(nk, 1073741825.0);   // beyond any cap
                 p.n[k] = (int)nk;
                 p.w[k] = wk / p.g[k];
             } else {
@@ -188,6 +189,7 @@ PCMS_HD inline void grid_params_compute(const double *lo, const double *hi, int 
         s *= p.n[k];
     }
     p.n_cells = s;
+    p.wm = wm;
     p.density = d_eff > 0 ? (double)n / vol : 0.0;
     *out = p;
 }
@@ -278,6 +280,23 @@ PCMS_HD PCMS_INLINE void load_src(const double *__restrict__ spts, int p, double
 // instead of eight); the mixed-precision searches classify candidates from it.
 PCMS_HD PCMS_INLINE constexpr int padded_dim32(int d) { return d; }
 
+// Floats of storage after the FP32 and fixed-point records, which a walk's
+// whole-word loads may read past the last record.
+constexpr int kPad32 = 16;
+#ifndef PCMS_HOST_EMULATION
+typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
+#endif
+
+// Square root to within 2^-22 (one instruction on the GPU).
+PCMS_HD PCMS_INLINE float sqrt_approx(float x)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __builtin_amdgcn_sqrtf(x);
+#else
+    return sqrt(x);
+#endif
+}
+
 template <int D>
 PCMS_HD PCMS_INLINE void load_src32(const float *__restrict__ s32, int p, float (&s)[D])
 {
@@ -312,6 +331,26 @@ PCMS_HD PCMS_INLINE void load_srcq(const uint32_t *__restrict__ sq, int p, uint3
 // floats would promote them and compute in FP64).
 PCMS_HD PCMS_INLINE float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 PCMS_HD PCMS_INLINE double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
+// Square root of x >= 0 in FP64: the reciprocal root's approximation, one
+// Goldschmidt step and two Newton corrections, as accurate as sqrt (the same
+// bits) for x from 1e-200 on; smaller ones, zero among them, give 1e-100.  It
+// leaves out the range scaling of sqrt, half of its instructions.
+PCMS_HD PCMS_INLINE double sqrt_unit(double x)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    x = fmax(x, 1e-200);
+    const double y = __builtin_amdgcn_rsq(x);
+    double g = x * y, h = 0.5 * y;
+    const double r = __builtin_fma(-h, g, 0.5);
+    g = __builtin_fma(g, r, g);
+    h = __builtin_fma(h, r, h);
+    g = __builtin_fma(__builtin_fma(-g, g, x), h, g);
+    return __builtin_fma(__builtin_fma(-g, g, x), h, g);
+#else
+    return sqrt(x < 1e-200 ? 1e-200 : x);
+#endif
+}
 
 // Two consecutive doubles from a 16-byte aligned address, in one load.
 PCMS_HD PCMS_INLINE void load_pair(const double *__restrict__ p, double &x, double &y)
@@ -361,7 +400,11 @@ struct Grp {
     T sum(T x) const { return pcms_emu_sum(emu, q, x); }
     template <class T>
     T min(T x) const { return pcms_emu_min(emu, q, x); }
+    bool all(bool p) const { return pcms_emu_min(emu, q, (int)p) != 0; }
     void sync() const { pcms_emu_sync(emu, q); }
+    // lane j's x, on every lane
+    template <class T>
+    T from(T x, int j) const { return (T)pcms_emu_sum(emu, q, q == j ? (double)x : 0.0); }
 #else
     __device__ PCMS_INLINE unsigned ballot(bool p) const
     {
@@ -390,6 +433,23 @@ struct Grp {
         }
         return x;
     }
+    __device__ PCMS_INLINE bool all(bool p) const { return min((int)p) != 0; }
+    // lane j's x, on every lane (j a constant once unrolled)
+    __device__ PCMS_INLINE uint32_t from(uint32_t x, int j) const
+    {
+        static_assert(G == 4, "quads");
+        const int v = (int)x;
+        return (uint32_t)(j == 0   ? __builtin_amdgcn_mov_dpp(v, 0x00, 0xf, 0xf, true)
+                          : j == 1 ? __builtin_amdgcn_mov_dpp(v, 0x55, 0xf, 0xf, true)
+                          : j == 2 ? __builtin_amdgcn_mov_dpp(v, 0xaa, 0xf, 0xf, true)
+                                   : __builtin_amdgcn_mov_dpp(v, 0xff, 0xf, 0xf, true));
+    }
+    __device__ PCMS_INLINE double from(double x, int j) const
+    {
+        const unsigned long long b = __builtin_bit_cast(unsigned long long, x);
+        const unsigned long long lo = from((uint32_t)b, j), hi = from((uint32_t)(b >> 32), j);
+        return __builtin_bit_cast(double, (hi << 32) | lo);
+    }
     // orders this lane's LDS accesses against the group's (one wavefront)
     __device__ PCMS_INLINE void sync() const
     {
@@ -403,6 +463,25 @@ struct Grp {
         return __builtin_popcount(m & ((1u << q) - 1u));
     }
 };
+
+#ifndef PCMS_HOST_EMULATION
+// One lane per target: the collectives are the lane's own values (the general
+// form's wave ballots and shifts cost six instructions per candidate).
+template <>
+struct Grp<1> {
+    int q;
+    PCMS_HD PCMS_INLINE unsigned ballot(bool p) const { return p ? 1u : 0u; }
+    template <class T>
+    PCMS_HD PCMS_INLINE T sum(T x) const { return x; }
+    template <class T>
+    PCMS_HD PCMS_INLINE T min(T x) const { return x; }
+    PCMS_HD PCMS_INLINE bool all(bool p) const { return p; }
+    template <class T>
+    PCMS_HD PCMS_INLINE T from(T x, int) const { return x; }
+    PCMS_HD PCMS_INLINE void sync() const {}
+    PCMS_HD PCMS_INLINE int below(unsigned) const { return 0; }
+};
+#endif
 
 // --- pieces of the stable radix-sort scatter (one 8-bit digit per pass) ------
 // Lanes of one wave holding the same digit: AND of the per-bit ballots.

@@ -1,8 +1,9 @@
 // Per-target work of the neighbour-list and field-transfer kernels, written
 // as host+device functions of (arguments, target slot, the target's LDS
 // words, lane group) so the CPU emulation build runs exactly this code.  The
-// G lanes of a target split the walks' candidates and the neighbours of the
-// fit passes; group sums combine their partial moments.
+// G lanes of a target split the walks' candidates and the loads of the fit
+// passes' neighbours and fields; each sums every neighbour, in list order, so
+// the results are the same bits for any G.
 //
 // Field transfer (PCMS paper, Section 3.2.1, Eq. 1): for target t with kept
 // sources s_e, weights w_e = phi(q_e), q_e = sqrt(D_e) / r, and monomials
@@ -225,51 +226,57 @@ struct KArgs {
 
 // LDS words of a target: its kept list (at most k_cap entries; in kNN mode
 // with k <= k_cap at most k - 1, since every kept D is below the k-th
-// smallest), which also holds the histogram and buffers of the radius search,
-// plus 8 for the bin of the k-th smallest D (kNN) or, where the cap is
-// expected to bind (growing radii, kNN beyond the cap), of the k_cap-th.  A
-// fixed radius keeps k_cap words: its rare capped targets take the general
-// bracketing path.
-PCMS_HD inline int target_words(int mode, int k, int k_cap)
+// smallest), which also holds the bins, row tables and buffers of the search,
+// plus kSpare where the k-th smallest D (kNN) or, where the cap is expected to
+// bind (growing radii, kNN beyond the cap), the k_cap-th is selected: 7 for
+// the sources ranked for it, and slack for the row table beside the list (with
+// 8 words 7 % of the targets of a kNN-40 search ran out of it, with 11 0.01 %;
+// more would cost the 4M-source kNN kernel its third wave per SIMD; in 4-D and
+// 5-D, whose lists outgrow the table's many rows, 24 keep the table of a capped
+// list from running out, and the five waves per CU of k_cap = 96).  A fixed
+// radius keeps k_cap words: its rare capped targets take the general path.
+PCMS_HD inline int target_words(int mode, int k, int k_cap, int dim = 3)
 {
-    if (mode == PCMS_RADIUS_KNN && k + 8 < k_cap) return k + 8;
+    const int spare = dim >= 4 ? 24 : 11;
+    if (mode == PCMS_RADIUS_KNN && k + 8 < k_cap) return k + spare;
     if (mode == PCMS_RADIUS_FIXED) return k_cap < 2 ? 2 : k_cap;
-    return k_cap + 8;
+    return k_cap + (k_cap > kMaxKcap - spare ? 8 : spare);
+}
+// Most entries of a kept list.
+PCMS_HD inline int target_kept(int mode, int k, int k_cap)
+{
+    return mode == PCMS_RADIUS_KNN && k + 8 < k_cap ? k + 8 : k_cap;
 }
 
 // Radius and kept list for one target; returns the status bits, the count
 // inside the radius, the number of kept list entries and r^2 (all uniform
-// across the group).  F32: the walks classify candidates from the FP32
-// records (same lists).
-template <int D, bool UNIT, int G, bool F32 = false, class S_>
+// across the group).
+template <int D, bool UNIT, int G, class S_>
 PCMS_HD PCMS_INLINE int select_target(S_ &S, const KArgs &a, int &n_found,
                                       int &n_kept, double &r2)
 {
     int st = PCMS_TGT_OK;
-    if (a.mode == PCMS_RADIUS_FIXED) {
-        r2 = a.r * a.r;
-        n_found = S.template collect<F32>(r2);
-    } else if (a.mode == PCMS_RADIUS_GROW) {
-        r2 = a.r * a.r;
-        n_found = S.template collect<F32>(r2);
-        int it = 0;
-        while (n_found < a.n_min && it < a.max_iter) {
-            r2 = 2.0 * r2;
-            ++it;
-            n_found = S.template collect<F32>(r2);
-        }
-        if (n_found < a.n_min) st = PCMS_TGT_RADIUS_EXHAUSTED;
-    } else {
+    bool listed = false;
+    if (a.mode == PCMS_RADIUS_KNN) {
         // n_found < k <= k_cap + 1 on the two-walk path, so no cap applies
-        if (!(a.k <= a.k_cap + 1 && S.template knn_select<F32>(a.k, r2, n_found))) {
-            r2 = S.knn_r2(a.k);
+        listed = a.k <= a.k_cap + 1 && S.knn_select(a.k, r2, n_found);
+        if (!listed) r2 = S.knn_r2(a.k);
+    } else {
+        r2 = a.r * a.r;
+    }
+    if (!listed) {
+        // (one call site, so that the walk is inlined once)
+        for (int it = 0;; ++it) {
             n_found = S.collect(r2);
+            if (a.mode != PCMS_RADIUS_GROW || n_found >= a.n_min || it >= a.max_iter) break;
+            r2 = 2.0 * r2;
         }
+        if (a.mode == PCMS_RADIUS_GROW && n_found < a.n_min) st = PCMS_TGT_RADIUS_EXHAUSTED;
     }
     n_kept = min(n_found, a.k_cap);
     if (n_found > a.k_cap) {
         st |= PCMS_TGT_CAPPED;
-        n_kept = S.template cap_collect<F32>(r2);
+        n_kept = S.cap_collect(r2, n_found);
     }
     return st;
 }
@@ -349,21 +356,44 @@ struct FitPts {
     }
 };
 
-// Loads the records of kept neighbours e0 + j G (j < B) of this lane at once,
-// with their sorted indices; slots past n repeat neighbour 0 and are flagged
-// invalid.
+// Loads the records of kept neighbours e0 + j G + q (j < B) of this lane at
+// once, with their sorted indices; slots past n repeat neighbour 0 and are
+// flagged invalid.
 template <int D, int G, int B, class S_, class FP>
 PCMS_HD PCMS_INLINE void load_neighbours(S_ &S, const FP &fp, int e0, int n,
                                          typename FP::Rec (&sb)[B][D], bool (&ok)[B], int (&pe)[B])
 {
 #pragma unroll
     for (int j = 0; j < B; ++j) {
-        const int e = e0 + j * G;
+        const int e = e0 + j * G + S.g.q;
         ok[j] = e < n;
         pe[j] = S.at(ok[j] ? e : 0);
     }
 #pragma unroll
     for (int j = 0; j < B; ++j) fp.load(pe[j], sb[j]);
+}
+
+// Calls f(e, u, ok) for the neighbours e = e0 .. e0 + G B - 1 in order, u the
+// offset (ok: e < n); the group's lanes load G B records at once and hand
+// them round.
+template <int D, int G, int B, class S_, class FP, class F>
+PCMS_HD PCMS_INLINE void each_neighbour(S_ &S, const FP &fp, int e0, int n, F &&f)
+{
+    typename FP::Rec sb[B][D];
+    bool ok[B];
+    int pe[B];
+    load_neighbours<D, G, B>(S, fp, e0, n, sb, ok, pe);
+#pragma unroll
+    for (int j = 0; j < B; ++j)
+#pragma unroll
+        for (int i = 0; i < G; ++i) {
+            typename FP::Rec r[D];
+#pragma unroll
+            for (int k = 0; k < D; ++k) r[k] = S.g.from(sb[j][k], i);
+            double u[D];
+            fp.offsets(r, u);
+            f(j * G + i, u, G == 1 ? ok[j] : e0 + j * G + i < n);
+        }
 }
 
 // Per-neighbour local data from its offset u = (t - s) g: monomials p of
@@ -381,7 +411,7 @@ PCMS_HD PCMS_INLINE void neighbour_data(const double (&u)[D], double inv_h, doub
         xi[k] = (T)(-u[k] * inv_h);
     }
     if constexpr (sizeof(T) == sizeof(double)) {
-        T q = sqrt((T)(d2 * inv_r2));
+        T q = sqrt_unit(d2 * inv_r2);
         w = weight_of<T>(weight, q);
     } else {
         // FP32 weights: 1 - q from 1 - q^2 formed in FP64, so that the weight
@@ -394,56 +424,68 @@ PCMS_HD PCMS_INLINE void neighbour_data(const double (&u)[D], double inv_h, doub
     monomials<D, P, T>(xi, p);
 }
 
-// Reference values of fields [l0, l0 + kFieldChunk) for a centred sum: the
-// first kept source's values in the mixed modes (centring leaves the fit
-// unchanged only without regularisation), else zero.
-template <bool MIXED, int FC = kFieldChunk, class S_>
-PCMS_HD PCMS_INLINE void field_refs(S_ &S, const KArgs &a, int l0, double (&fref)[FC])
+// A chunk of FC fields is summed in pairs (16-byte words of the field
+// records), pair h G + q by lane q.
+template <int FC, int G>
+constexpr int kPairs = (FC / 2 + G - 1) / G;
+
+// Reference values of the lane's pairs of fields [l0, l0 + FC) for a centred
+// sum: the first kept source's values in the mixed modes (centring leaves the
+// fit unchanged only without regularisation), else zero.
+template <bool MIXED, int G, int FC = kFieldChunk, class S_>
+PCMS_HD PCMS_INLINE void field_refs(S_ &S, const KArgs &a, int l0, double (&fref)[2 * kPairs<FC, G>])
 {
     const double *sv0 = a.svals + (size_t)S.at(0) * a.nfs;
 #pragma unroll
-    for (int l = 0; l < FC; ++l)
-        fref[l] = (MIXED && a.lambda == 0.0 && l0 + l < a.nf) ? sv0[l0 + l] : 0.0;
+    for (int i = 0; i < 2 * kPairs<FC, G>; ++i) {
+        const int l = 2 * ((i / 2) * G + S.g.q) + (i & 1);
+        fref[i] = (MIXED && a.lambda == 0.0 && l < FC && l0 + l < a.nf) ? sv0[l0 + l] : 0.0;
+    }
 }
 
-// One pass over the n kept sources with the coefficients y: acc[l] = sum_e
-// w_e (p_e . y) (f_{e, l0 + l} - fref[l]), per lane (the caller sums over the
-// group).  B neighbours' loads are issued together.
+// The lane's pairs of fields [l0, l0 + FC) of neighbours e0 .. e0 + G B - 1
+// (zero past nfs); the sources are those of slots e, or of slot 0 past n.
+template <int G, int B, int FC, class S_>
+PCMS_HD PCMS_INLINE void load_fields(S_ &S, const KArgs &a, int e0, int n, int l0,
+                                     double (&fv)[G * B][2 * kPairs<FC, G>])
+{
+#pragma unroll
+    for (int j = 0; j < G * B; ++j) {
+        const double *sv = a.svals + (size_t)S.at(e0 + j < n ? e0 + j : 0) * a.nfs + l0;
+#pragma unroll
+        for (int h = 0; h < kPairs<FC, G>; ++h) {
+            const int l = 2 * (h * G + S.g.q);
+            fv[j][2 * h] = fv[j][2 * h + 1] = 0.0;
+            if (l < FC && l0 + l < a.nfs) load_pair(sv + l, fv[j][2 * h], fv[j][2 * h + 1]);
+        }
+    }
+}
+
+// One pass over the n kept sources with the coefficients y: acc = sum_e
+// w_e (p_e . y) (f_e - fref) of the lane's pairs of fields [l0, l0 +
+// kFieldChunk).  G B neighbours' loads are issued together.
 template <int D, int P, int G, int B, class S_, class FP>
 PCMS_HD PCMS_INLINE void field_pass(S_ &S, const KArgs &a, const FP &fp, int n, double inv_h,
                                     double inv_r2, const double (&y)[Basis<D, P>::M], int l0,
-                                    const double (&fref)[kFieldChunk], double (&acc)[kFieldChunk])
+                                    const double (&fref)[2 * kPairs<kFieldChunk, G>],
+                                    double (&acc)[2 * kPairs<kFieldChunk, G>])
 {
-    constexpr int M = Basis<D, P>::M;
+    constexpr int M = Basis<D, P>::M, NF = 2 * kPairs<kFieldChunk, G>;
 #pragma unroll
-    for (int l = 0; l < kFieldChunk; ++l) acc[l] = 0.0;
-    for (int e0 = S.g.q; e0 < n; e0 += G * B) {
-        typename FP::Rec sb[B][D];
-        bool ok[B];
-        int pe[B];
-        load_neighbours<D, G, B>(S, fp, e0, n, sb, ok, pe);
-        double fv[B][kFieldChunk];
-#pragma unroll
-        for (int j = 0; j < B; ++j) {
-            const double *sv = a.svals + (size_t)pe[j] * a.nfs + l0;
-#pragma unroll
-            for (int h = 0; h < kFieldChunk / 2; ++h) {
-                fv[j][2 * h] = fv[j][2 * h + 1] = 0.0;
-                if (l0 + 2 * h < a.nfs) load_pair(sv + 2 * h, fv[j][2 * h], fv[j][2 * h + 1]);
-            }
-        }
-#pragma unroll
-        for (int j = 0; j < B; ++j) {
-            double u[D], p[M], w;
-            fp.offsets(sb[j], u);
+    for (int l = 0; l < NF; ++l) acc[l] = 0.0;
+    for (int e0 = 0; e0 < n; e0 += G * B) {
+        double fv[G * B][NF];
+        load_fields<G, B, kFieldChunk>(S, a, e0, n, l0, fv);
+        each_neighbour<D, G, B>(S, fp, e0, n, [&](int j, const double (&u)[D], bool ok) {
+            double p[M], w;
             neighbour_data<D, P, double>(u, inv_h, inv_r2, a.weight, p, w);
             double py = 0.0;
 #pragma unroll
             for (int v = 0; v < M; ++v) py = __builtin_fma(p[v], y[v], py);
-            const double N = ok[j] ? w * py : 0.0;
+            const double N = ok ? w * py : 0.0;
 #pragma unroll
-            for (int l = 0; l < kFieldChunk; ++l) acc[l] = __builtin_fma(N, fv[j][l] - fref[l], acc[l]);
-        }
+            for (int l = 0; l < NF; ++l) acc[l] = __builtin_fma(N, fv[j][l] - fref[l], acc[l]);
+        });
     }
 }
 
@@ -472,15 +514,14 @@ PCMS_HD PCMS_INLINE int refine_update(double (&y)[M], const TA (&d)[M], int step
 }
 
 // The correction d = R^{-1} R^{-T} (e_0 - lambda y + res) of a residual
-// partial sum res = -sum_e w_e (p_e . y) p_e (summed over the group here),
-// solved in the arithmetic of the factor.
-template <int M, int G, typename TA>
+// sum res = -sum_e w_e (p_e . y) p_e, solved in the arithmetic of the factor.
+template <int M, typename TA>
 PCMS_HD PCMS_INLINE void refine_correction(const TA (&R)[M * (M + 1) / 2], const TA (&idg)[M],
                                            const double (&y)[M], const double (&res)[M],
-                                           double lambda, Grp<G> g, TA (&d)[M])
+                                           double lambda, TA (&d)[M])
 {
 #pragma unroll
-    for (int u = 0; u < M; ++u) d[u] = (TA)(g.sum(res[u]) + ((u == 0 ? 1.0 : 0.0) - lambda * y[u]));
+    for (int u = 0; u < M; ++u) d[u] = (TA)(res[u] + ((u == 0 ? 1.0 : 0.0) - lambda * y[u]));
     chol_solve_in<M, TA>(R, idg, d);
 }
 
@@ -500,26 +541,19 @@ PCMS_HD PCMS_INLINE bool refine_steps(S_ &S, const KArgs &a, const FP &fp, int n
         double res[M];
 #pragma unroll
         for (int u = 0; u < M; ++u) res[u] = 0.0;
-        for (int e0 = S.g.q; e0 < n; e0 += G * K) {
-            typename FP::Rec sb[K][D];
-            bool okn[K];
-            int pe[K];
-            load_neighbours<D, G, K>(S, fp, e0, n, sb, okn, pe);
-#pragma unroll
-            for (int j = 0; j < K; ++j) {
-                double uo[D], p[M], w;
-                fp.offsets(sb[j], uo);
+        for (int e0 = 0; e0 < n; e0 += G * K)
+            each_neighbour<D, G, K>(S, fp, e0, n, [&](int, const double (&uo)[D], bool ok) {
+                double p[M], w;
                 neighbour_data<D, P, double>(uo, inv_h, inv_r2, a.weight, p, w);
                 double py = 0.0;
 #pragma unroll
                 for (int u = 0; u < M; ++u) py = __builtin_fma(p[u], y[u], py);
-                const double c = okn[j] ? -w * py : 0.0;
+                const double c = ok ? -w * py : 0.0;
 #pragma unroll
                 for (int u = 0; u < M; ++u) res[u] = __builtin_fma(c, p[u], res[u]);
-            }
-        }
+            });
         TA d[M];
-        refine_correction<M, G, TA>(R, idg, y, res, a.lambda, S.g, d);
+        refine_correction<M, TA>(R, idg, y, res, a.lambda, d);
         const int r = refine_update<M, TA>(y, d, step, nd_prev);
         if (r == 0) return true;
         if (r == 2) return false;
@@ -537,47 +571,34 @@ PCMS_HD PCMS_INLINE bool refine_steps(S_ &S, const KArgs &a, const FP &fp, int n
 template <int D, int P, int G, int B, int FC, class S_, class FP>
 PCMS_HD PCMS_INLINE void field_pass_fused(S_ &S, const KArgs &a, const FP &fp, int n, double inv_h,
                                           double inv_r2, const double (&y)[Basis<D, P>::M], int l0,
-                                          const double (&fref)[FC], double (&acc)[FC],
+                                          const double (&fref)[2 * kPairs<FC, G>],
+                                          double (&acc)[2 * kPairs<FC, G>],
                                           double (&res)[Basis<D, P>::M],
-                                          float (&Bm)[Basis<D, P>::M][FC])
+                                          float (&Bm)[Basis<D, P>::M][2 * kPairs<FC, G>])
 {
-    constexpr int M = Basis<D, P>::M;
+    constexpr int M = Basis<D, P>::M, NF = 2 * kPairs<FC, G>;
 #pragma unroll
-    for (int l = 0; l < FC; ++l) acc[l] = 0.0;
+    for (int l = 0; l < NF; ++l) acc[l] = 0.0;
 #pragma unroll
     for (int u = 0; u < M; ++u) {
         res[u] = 0.0;
 #pragma unroll
-        for (int l = 0; l < FC; ++l) Bm[u][l] = 0.0f;
+        for (int l = 0; l < NF; ++l) Bm[u][l] = 0.0f;
     }
-    for (int e0 = S.g.q; e0 < n; e0 += G * B) {
-        typename FP::Rec sb[B][D];
-        bool ok[B];
-        int pe[B];
-        load_neighbours<D, G, B>(S, fp, e0, n, sb, ok, pe);
-        double fv[B][FC];
-#pragma unroll
-        for (int j = 0; j < B; ++j) {
-            const double *sv = a.svals + (size_t)pe[j] * a.nfs + l0;
-#pragma unroll
-            for (int h = 0; h < FC / 2; ++h) {
-                fv[j][2 * h] = fv[j][2 * h + 1] = 0.0;
-                if (l0 + 2 * h < a.nfs) load_pair(sv + 2 * h, fv[j][2 * h], fv[j][2 * h + 1]);
-            }
-        }
-#pragma unroll
-        for (int j = 0; j < B; ++j) {
-            double u[D], p[M], w;
-            fp.offsets(sb[j], u);
+    for (int e0 = 0; e0 < n; e0 += G * B) {
+        double fv[G * B][NF];
+        load_fields<G, B, FC>(S, a, e0, n, l0, fv);
+        each_neighbour<D, G, B>(S, fp, e0, n, [&](int j, const double (&u)[D], bool ok) {
+            double p[M], w;
             neighbour_data<D, P, double>(u, inv_h, inv_r2, a.weight, p, w);
-            w = ok[j] ? w : 0.0;
+            w = ok ? w : 0.0;
             double py = 0.0;
 #pragma unroll
             for (int v = 0; v < M; ++v) py = __builtin_fma(p[v], y[v], py);
             const double N = w * py;
-            float wf[FC];
+            float wf[NF];
 #pragma unroll
-            for (int l = 0; l < FC; ++l) {
+            for (int l = 0; l < NF; ++l) {
                 const double df = fv[j][l] - fref[l];
                 acc[l] = __builtin_fma(N, df, acc[l]);
                 wf[l] = (float)(w * df);
@@ -587,31 +608,31 @@ PCMS_HD PCMS_INLINE void field_pass_fused(S_ &S, const KArgs &a, const FP &fp, i
                 res[v] = __builtin_fma(-N, p[v], res[v]);
                 const float pv = (float)p[v];
 #pragma unroll
-                for (int l = 0; l < FC; ++l) Bm[v][l] = fma_t(pv, wf[l], Bm[v][l]);
+                for (int l = 0; l < NF; ++l) Bm[v][l] = fma_t(pv, wf[l], Bm[v][l]);
             }
-        }
+        });
     }
 }
 
-// Group sums of a field chunk, written to the target's outputs (or to its
-// staged record, whose padding past nf receives zeros).
+// The lane's pairs of a field chunk, written to the target's outputs (or to
+// its staged record, whose padding past nf receives zeros).
 template <int G, int FC = kFieldChunk>
-PCMS_HD PCMS_INLINE void write_fields(const KArgs &a, int ti, int l0, const double (&acc)[FC],
-                                      const double (&fref)[FC], Grp<G> g)
+PCMS_HD PCMS_INLINE void write_fields(const KArgs &a, int ti, int l0,
+                                      const double (&acc)[2 * kPairs<FC, G>],
+                                      const double (&fref)[2 * kPairs<FC, G>], Grp<G> g)
 {
-    double v[FC];
 #pragma unroll
-    for (int l = 0; l < FC; ++l) v[l] = g.sum(acc[l]) + fref[l];
-    if (a.stage) {
-        double *rec = a.stage + (size_t)ti * a.nfs + l0;
-#pragma unroll
-        for (int h = 0; h < FC / 2; ++h)
-            if (l0 + 2 * h < a.nfs && (h % G) == g.q) store_pair(rec + 2 * h, v[2 * h], v[2 * h + 1]);
-        return;
+    for (int h = 0; h < kPairs<FC, G>; ++h) {
+        const int l = 2 * (h * G + g.q);
+        const double v0 = acc[2 * h] + fref[2 * h], v1 = acc[2 * h + 1] + fref[2 * h + 1];
+        if (l >= FC) continue;
+        if (a.stage) {
+            if (l0 + l < a.nfs) store_pair(a.stage + (size_t)ti * a.nfs + l0 + l, v0, v1);
+        } else {
+            if (l0 + l < a.nf) a.out[(size_t)(l0 + l) * a.n_tgt + ti] = v0;
+            if (l0 + l + 1 < a.nf) a.out[(size_t)(l0 + l + 1) * a.n_tgt + ti] = v1;
+        }
     }
-#pragma unroll
-    for (int l = 0; l < FC; ++l)
-        if (l0 + l < a.nf && (l % G) == g.q) a.out[(size_t)(l0 + l) * a.n_tgt + ti] = v[l];
 }
 
 // Field transfer of the target at sorted slot i; returns its status.
@@ -640,7 +661,6 @@ PCMS_HD PCMS_INLINE int xfer_target(const KArgs &a, const GridParams &gp, int i,
     // the position for any rounding of it).
     using FQ = FitPts<D, UNIT, REFINE>;
     using FP = FitPts<D, UNIT, false>;
-    using RecQ = typename FQ::Rec;
     // small bases: the first refinement step of MIXED_REFINE rides on the
     // evaluation pass of the first kFused fields (their FP32 field moments
     // fit in registers)
@@ -653,9 +673,7 @@ PCMS_HD PCMS_INLINE int xfer_target(const KArgs &a, const GridParams &gp, int i,
     load_point<D>(a.tgt, ti, S.t);
     int n_found, n;
     double r2;
-    // FP32 walks where they save loads: a point's FP32 record is one load (at
-    // most 16 bytes) and its FP64 record is two (3-D and 4-D)
-    int st = select_target<D, UNIT, G, MIXED && D >= 3 && D <= 4>(S, a, n_found, n, r2);
+    int st = select_target<D, UNIT, G>(S, a, n_found, n, r2);
     if ((st & 0xF) == PCMS_TGT_OK && n < M) st |= PCMS_TGT_UNDERDETERMINED;
     double y[M];
     if ((st & 0xF) == PCMS_TGT_OK) {
@@ -663,23 +681,15 @@ PCMS_HD PCMS_INLINE int xfer_target(const KArgs &a, const GridParams &gp, int i,
         const double inv_r2 = 1.0 / r2;
         const FP fp(a, gp, S.t);
         const FQ fq(a, gp, S.t);
-        // moment matrix G = sum w p p^T (upper triangle, in TA); lane q takes
-        // the neighbours e = q, q + G, ... and the group sums the partials
+        // moment matrix G = sum w p p^T (upper triangle, in TA)
         TA Gm[MM];
 #pragma unroll
         for (int j = 0; j < MM; ++j) Gm[j] = TA(0);
-        for (int e0 = g.q; e0 < n; e0 += G * kAsm) {
-            RecQ sb[kAsm][D];
-            bool ok[kAsm];
-            int pe[kAsm];
-            load_neighbours<D, G, kAsm>(S, fq, e0, n, sb, ok, pe);
-#pragma unroll
-            for (int j = 0; j < kAsm; ++j) {
-                double uo[D];
-                fq.offsets(sb[j], uo);
+        for (int e0 = 0; e0 < n; e0 += G * kAsm)
+            each_neighbour<D, G, kAsm>(S, fq, e0, n, [&](int, const double (&uo)[D], bool in) {
                 TA p[M], w;
                 neighbour_data<D, P, TA>(uo, inv_h, inv_r2, a.weight, p, w);
-                w = ok[j] ? w : TA(0);
+                w = in ? w : TA(0);
 #pragma unroll
                 for (int u = 0; u < M; ++u) {
                     TA wp = w * p[u];
@@ -687,10 +697,7 @@ PCMS_HD PCMS_INLINE int xfer_target(const KArgs &a, const GridParams &gp, int i,
                     for (int v = u; v < M; ++v)
                         Gm[tri<M>(u, v)] = fma_t(wp, p[v], Gm[tri<M>(u, v)]);
                 }
-            }
-        }
-#pragma unroll
-        for (int j = 0; j < MM; ++j) Gm[j] = g.sum(Gm[j]);
+            });
         bool ok;
         TA idg[M];   // inverse diagonal of the FP32 factor (MIXED_REFINE)
 #pragma unroll
@@ -735,7 +742,7 @@ PCMS_HD PCMS_INLINE int xfer_target(const KArgs &a, const GridParams &gp, int i,
         if (!ok) st |= PCMS_TGT_SINGULAR;
         if (EMIT) {
             if ((st & 0xF) == PCMS_TGT_OK) {
-                for (int e0 = g.q; e0 < n; e0 += G * kApply) {
+                for (int e0 = 0; e0 < n; e0 += G * kApply) {
                     Rec sb[kApply][D];
                     bool okn[kApply];
                     int pe[kApply];
@@ -749,7 +756,7 @@ PCMS_HD PCMS_INLINE int xfer_target(const KArgs &a, const GridParams &gp, int i,
 #pragma unroll
                         for (int u = 0; u < M; ++u) py = __builtin_fma(p[u], y[u], py);
                         if (okn[j]) {
-                            const size_t at = (size_t)(e0 + j * G) * a.n_tgt + i;
+                            const size_t at = (size_t)(e0 + j * G + g.q) * a.n_tgt + i;
                             a.op_w[at] = w * py;
                             a.op_c[at] = pe[j];
                         }
@@ -763,18 +770,19 @@ PCMS_HD PCMS_INLINE int xfer_target(const KArgs &a, const GridParams &gp, int i,
                 // when one step is enough, the chunk's values are those of
                 // the refined y; otherwise refinement continues with passes
                 // of its own and the chunk is evaluated again
-                double acc[kFused], fref[kFused], res[M];
-                float Bm[M][kFused];
-                field_refs<MIXED, kFused>(S, a, 0, fref);
+                constexpr int NF = 2 * kPairs<kFused, G>;
+                double acc[NF], fref[NF], res[M];
+                float Bm[M][NF];
+                field_refs<MIXED, G, kFused>(S, a, 0, fref);
                 field_pass_fused<D, P, G, 1, kFused>(S, a, fp, n, inv_h, inv_r2, y, 0, fref, acc,
                                                      res, Bm);
                 TA d[M];
-                refine_correction<M, G, TA>(Gm, idg, y, res, a.lambda, g, d);
+                refine_correction<M, TA>(Gm, idg, y, res, a.lambda, d);
                 double nd = 0.0;
                 const int r = refine_update<M, TA>(y, d, 0, nd);
                 if (r == 0) {
 #pragma unroll
-                    for (int l = 0; l < kFused; ++l) {
+                    for (int l = 0; l < NF; ++l) {
                         double c = 0.0;
 #pragma unroll
                         for (int u = 0; u < M; ++u) c = __builtin_fma((double)d[u], (double)Bm[u][l], c);
@@ -789,8 +797,8 @@ PCMS_HD PCMS_INLINE int xfer_target(const KArgs &a, const GridParams &gp, int i,
                 }
             }
             for (int l0 = l_begin; l0 < a.nf; l0 += kFieldChunk) {
-                double acc[kFieldChunk], fref[kFieldChunk];
-                field_refs<MIXED>(S, a, l0, fref);
+                double acc[2 * kPairs<kFieldChunk, G>], fref[2 * kPairs<kFieldChunk, G>];
+                field_refs<MIXED, G>(S, a, l0, fref);
                 field_pass<D, P, G, kApply>(S, a, fp, n, inv_h, inv_r2, y, l0, fref, acc);
                 write_fields<G>(a, ti, l0, acc, fref, g);
             }

@@ -12,28 +12,27 @@
 
 namespace pcms {
 
-// Lanes per target (G consecutive lanes of a wave); the block's targets are
-// consecutive in processing order and each owns `stride` LDS words.
-#ifndef PCMS_LANES_PER_TARGET
-#define PCMS_LANES_PER_TARGET 1
-#endif
-constexpr int kGroup = PCMS_LANES_PER_TARGET;
+// Lanes per target (G consecutive lanes of a wave): one, or four for calls of
+// few targets (target_lanes in mls.hip).  The block's targets are consecutive
+// in processing order and each owns `stride` LDS words.
+constexpr int kQuad = 4;
 
 using KernelFn = void (*)(KArgs);
 
-// Kernel of dimension D for (degree, precision, unit metric); defined in
-// mls_d<D>.hip, and the same on an LBVH in bvh_d<D>.hip.
-template <int D>
+// Kernel of dimension D and G lanes per target for (degree, precision, unit
+// metric); defined in mls_d<D>.hip and, for quads, mls4_d<D>.hip; the same on
+// an LBVH in bvh_d<D>.hip.
+template <int D, int G>
 KernelFn transfer_kernel(int degree, int precision, bool unit);
-template <int D>
+template <int D, int G>
 KernelFn nbr_kernel(bool unit);
 template <int D>
 KernelFn transfer_kernel_bvh(int degree, int precision, bool unit);
 template <int D>
 KernelFn nbr_kernel_bvh(bool unit);
-// The operator-emission variant of transfer_kernel; defined in op_d<D>.hip,
-// and on an LBVH in bvh_op_d<D>.hip.
-template <int D>
+// The operator-emission variant of transfer_kernel; defined in op_d<D>.hip
+// and op4_d<D>.hip, and on an LBVH in bvh_op_d<D>.hip.
+template <int D, int G>
 KernelFn operator_kernel(int degree, int precision, bool unit);
 template <int D>
 KernelFn operator_kernel_bvh(int degree, int precision, bool unit);
@@ -113,42 +112,42 @@ k_operator(KArgs a)
     add_summary(a.summary, st, active && g.q == 0);
 }
 
-template <int D, int P, bool UNIT, bool BVH = false>
+template <int D, int P, bool UNIT, int G, bool BVH = false>
 KernelFn pick_prec(int precision)
 {
-    return precision == PCMS_FP64  ? (KernelFn)k_transfer<D, P, PCMS_FP64, UNIT, kGroup, BVH>
-         : precision == PCMS_MIXED ? (KernelFn)k_transfer<D, P, PCMS_MIXED, UNIT, kGroup, BVH>
-                                   : (KernelFn)k_transfer<D, P, PCMS_MIXED_REFINE, UNIT, kGroup, BVH>;
+    return precision == PCMS_FP64  ? (KernelFn)k_transfer<D, P, PCMS_FP64, UNIT, G, BVH>
+         : precision == PCMS_MIXED ? (KernelFn)k_transfer<D, P, PCMS_MIXED, UNIT, G, BVH>
+                                   : (KernelFn)k_transfer<D, P, PCMS_MIXED_REFINE, UNIT, G, BVH>;
 }
 
-template <int D, int P, bool UNIT, bool BVH = false>
+template <int D, int P, bool UNIT, int G, bool BVH = false>
 KernelFn pick_prec_op(int precision)
 {
-    return precision == PCMS_FP64  ? (KernelFn)k_operator<D, P, PCMS_FP64, UNIT, kGroup, BVH>
-         : precision == PCMS_MIXED ? (KernelFn)k_operator<D, P, PCMS_MIXED, UNIT, kGroup, BVH>
-                                   : (KernelFn)k_operator<D, P, PCMS_MIXED_REFINE, UNIT, kGroup, BVH>;
+    return precision == PCMS_FP64  ? (KernelFn)k_operator<D, P, PCMS_FP64, UNIT, G, BVH>
+         : precision == PCMS_MIXED ? (KernelFn)k_operator<D, P, PCMS_MIXED, UNIT, G, BVH>
+                                   : (KernelFn)k_operator<D, P, PCMS_MIXED_REFINE, UNIT, G, BVH>;
 }
 
 }  // namespace
 
 // Body of the per-dimension definitions.
-#define PCMS_DEFINE_DIM_KERNELS(DD)                                                    \
+#define PCMS_DEFINE_DIM_KERNELS(DD, GG)                                                \
     template <>                                                                        \
-    KernelFn transfer_kernel<DD>(int degree, int precision, bool unit)                 \
+    KernelFn transfer_kernel<DD, GG>(int degree, int precision, bool unit)             \
     {                                                                                  \
         if (unit)                                                                      \
-            return degree == 0 ? pick_prec<DD, 0, true>(precision)                     \
-                 : degree == 1 ? pick_prec<DD, 1, true>(precision)                     \
-                               : pick_prec<DD, 2, true>(precision);                    \
-        return degree == 0 ? pick_prec<DD, 0, false>(precision)                        \
-             : degree == 1 ? pick_prec<DD, 1, false>(precision)                        \
-                           : pick_prec<DD, 2, false>(precision);                       \
+            return degree == 0 ? pick_prec<DD, 0, true, GG>(precision)                 \
+                 : degree == 1 ? pick_prec<DD, 1, true, GG>(precision)                 \
+                               : pick_prec<DD, 2, true, GG>(precision);                \
+        return degree == 0 ? pick_prec<DD, 0, false, GG>(precision)                    \
+             : degree == 1 ? pick_prec<DD, 1, false, GG>(precision)                    \
+                           : pick_prec<DD, 2, false, GG>(precision);                   \
     }                                                                                  \
     template <>                                                                        \
-    KernelFn nbr_kernel<DD>(bool unit)                                                 \
+    KernelFn nbr_kernel<DD, GG>(bool unit)                                             \
     {                                                                                  \
-        return unit ? (KernelFn)k_neighbors<DD, true, kGroup>                          \
-                    : (KernelFn)k_neighbors<DD, false, kGroup>;                        \
+        return unit ? (KernelFn)k_neighbors<DD, true, GG>                              \
+                    : (KernelFn)k_neighbors<DD, false, GG>;                            \
     }
 
 #define PCMS_DEFINE_DIM_BVH(DD)                                                        \
@@ -156,18 +155,18 @@ KernelFn pick_prec_op(int precision)
     KernelFn transfer_kernel_bvh<DD>(int degree, int precision, bool unit)             \
     {                                                                                  \
         if (unit)                                                                      \
-            return degree == 0 ? pick_prec<DD, 0, true, true>(precision)               \
-                 : degree == 1 ? pick_prec<DD, 1, true, true>(precision)               \
-                               : pick_prec<DD, 2, true, true>(precision);              \
-        return degree == 0 ? pick_prec<DD, 0, false, true>(precision)                  \
-             : degree == 1 ? pick_prec<DD, 1, false, true>(precision)                  \
-                           : pick_prec<DD, 2, false, true>(precision);                 \
+            return degree == 0 ? pick_prec<DD, 0, true, 1, true>(precision)            \
+                 : degree == 1 ? pick_prec<DD, 1, true, 1, true>(precision)            \
+                               : pick_prec<DD, 2, true, 1, true>(precision);           \
+        return degree == 0 ? pick_prec<DD, 0, false, 1, true>(precision)               \
+             : degree == 1 ? pick_prec<DD, 1, false, 1, true>(precision)               \
+                           : pick_prec<DD, 2, false, 1, true>(precision);              \
     }                                                                                  \
     template <>                                                                        \
     KernelFn nbr_kernel_bvh<DD>(bool unit)                                             \
     {                                                                                  \
-        return unit ? (KernelFn)k_neighbors<DD, true, kGroup, true>                    \
-                    : (KernelFn)k_neighbors<DD, false, kGroup, true>;                  \
+        return unit ? (KernelFn)k_neighbors<DD, true, 1, true>                         \
+                    : (KernelFn)k_neighbors<DD, false, 1, true>;                       \
     }
 
 #define PCMS_DEFINE_DIM_OPERATOR_BVH(DD)                                               \
@@ -175,25 +174,25 @@ KernelFn pick_prec_op(int precision)
     KernelFn operator_kernel_bvh<DD>(int degree, int precision, bool unit)             \
     {                                                                                  \
         if (unit)                                                                      \
-            return degree == 0 ? pick_prec_op<DD, 0, true, true>(precision)            \
-                 : degree == 1 ? pick_prec_op<DD, 1, true, true>(precision)            \
-                               : pick_prec_op<DD, 2, true, true>(precision);           \
-        return degree == 0 ? pick_prec_op<DD, 0, false, true>(precision)               \
-             : degree == 1 ? pick_prec_op<DD, 1, false, true>(precision)               \
-                           : pick_prec_op<DD, 2, false, true>(precision);              \
+            return degree == 0 ? pick_prec_op<DD, 0, true, 1, true>(precision)         \
+                 : degree == 1 ? pick_prec_op<DD, 1, true, 1, true>(precision)         \
+                               : pick_prec_op<DD, 2, true, 1, true>(precision);        \
+        return degree == 0 ? pick_prec_op<DD, 0, false, 1, true>(precision)            \
+             : degree == 1 ? pick_prec_op<DD, 1, false, 1, true>(precision)            \
+                           : pick_prec_op<DD, 2, false, 1, true>(precision);           \
     }
 
-#define PCMS_DEFINE_DIM_OPERATOR(DD)                                                   \
+#define PCMS_DEFINE_DIM_OPERATOR(DD, GG)                                               \
     template <>                                                                        \
-    KernelFn operator_kernel<DD>(int degree, int precision, bool unit)                 \
+    KernelFn operator_kernel<DD, GG>(int degree, int precision, bool unit)             \
     {                                                                                  \
         if (unit)                                                                      \
-            return degree == 0 ? pick_prec_op<DD, 0, true>(precision)                  \
-                 : degree == 1 ? pick_prec_op<DD, 1, true>(precision)                  \
-                               : pick_prec_op<DD, 2, true>(precision);                 \
-        return degree == 0 ? pick_prec_op<DD, 0, false>(precision)                     \
-             : degree == 1 ? pick_prec_op<DD, 1, false>(precision)                     \
-                           : pick_prec_op<DD, 2, false>(precision);                    \
+            return degree == 0 ? pick_prec_op<DD, 0, true, GG>(precision)              \
+                 : degree == 1 ? pick_prec_op<DD, 1, true, GG>(precision)              \
+                               : pick_prec_op<DD, 2, true, GG>(precision);             \
+        return degree == 0 ? pick_prec_op<DD, 0, false, GG>(precision)                 \
+             : degree == 1 ? pick_prec_op<DD, 1, false, GG>(precision)                 \
+                           : pick_prec_op<DD, 2, false, GG>(precision);                \
     }
 
 }  // namespace pcms

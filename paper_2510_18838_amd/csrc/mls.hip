@@ -18,7 +18,7 @@ __global__ void k_zero_ints(int32_t *p, int n)
     if (i < n) p[i] = 0;
 }
 
-KernelFn xfer_for(int d, int p, int precision, bool unit, bool bvh)
+KernelFn xfer_for(int d, int p, int precision, bool unit, bool bvh, bool quad)
 {
     if (bvh) {
         switch (d) {
@@ -31,16 +31,16 @@ KernelFn xfer_for(int d, int p, int precision, bool unit, bool bvh)
         return nullptr;
     }
     switch (d) {
-    case 1: return transfer_kernel<1>(p, precision, unit);
-    case 2: return transfer_kernel<2>(p, precision, unit);
-    case 3: return transfer_kernel<3>(p, precision, unit);
-    case 4: return transfer_kernel<4>(p, precision, unit);
-    case 5: return transfer_kernel<5>(p, precision, unit);
+    case 1: return quad ? transfer_kernel<1, kQuad>(p, precision, unit) : transfer_kernel<1, 1>(p, precision, unit);
+    case 2: return quad ? transfer_kernel<2, kQuad>(p, precision, unit) : transfer_kernel<2, 1>(p, precision, unit);
+    case 3: return quad ? transfer_kernel<3, kQuad>(p, precision, unit) : transfer_kernel<3, 1>(p, precision, unit);
+    case 4: return quad ? transfer_kernel<4, kQuad>(p, precision, unit) : transfer_kernel<4, 1>(p, precision, unit);
+    case 5: return quad ? transfer_kernel<5, kQuad>(p, precision, unit) : transfer_kernel<5, 1>(p, precision, unit);
     }
     return nullptr;
 }
 
-KernelFn op_for(int d, int p, int precision, bool unit, bool bvh)
+KernelFn op_for(int d, int p, int precision, bool unit, bool bvh, bool quad)
 {
     if (bvh) {
         switch (d) {
@@ -53,16 +53,16 @@ KernelFn op_for(int d, int p, int precision, bool unit, bool bvh)
         return nullptr;
     }
     switch (d) {
-    case 1: return operator_kernel<1>(p, precision, unit);
-    case 2: return operator_kernel<2>(p, precision, unit);
-    case 3: return operator_kernel<3>(p, precision, unit);
-    case 4: return operator_kernel<4>(p, precision, unit);
-    case 5: return operator_kernel<5>(p, precision, unit);
+    case 1: return quad ? operator_kernel<1, kQuad>(p, precision, unit) : operator_kernel<1, 1>(p, precision, unit);
+    case 2: return quad ? operator_kernel<2, kQuad>(p, precision, unit) : operator_kernel<2, 1>(p, precision, unit);
+    case 3: return quad ? operator_kernel<3, kQuad>(p, precision, unit) : operator_kernel<3, 1>(p, precision, unit);
+    case 4: return quad ? operator_kernel<4, kQuad>(p, precision, unit) : operator_kernel<4, 1>(p, precision, unit);
+    case 5: return quad ? operator_kernel<5, kQuad>(p, precision, unit) : operator_kernel<5, 1>(p, precision, unit);
     }
     return nullptr;
 }
 
-KernelFn nbr_for(int d, bool unit, bool bvh)
+KernelFn nbr_for(int d, bool unit, bool bvh, bool quad)
 {
     if (bvh) {
         switch (d) {
@@ -75,11 +75,11 @@ KernelFn nbr_for(int d, bool unit, bool bvh)
         return nullptr;
     }
     switch (d) {
-    case 1: return nbr_kernel<1>(unit);
-    case 2: return nbr_kernel<2>(unit);
-    case 3: return nbr_kernel<3>(unit);
-    case 4: return nbr_kernel<4>(unit);
-    case 5: return nbr_kernel<5>(unit);
+    case 1: return quad ? nbr_kernel<1, kQuad>(unit) : nbr_kernel<1, 1>(unit);
+    case 2: return quad ? nbr_kernel<2, kQuad>(unit) : nbr_kernel<2, 1>(unit);
+    case 3: return quad ? nbr_kernel<3, kQuad>(unit) : nbr_kernel<3, 1>(unit);
+    case 4: return quad ? nbr_kernel<4, kQuad>(unit) : nbr_kernel<4, 1>(unit);
+    case 5: return quad ? nbr_kernel<5, kQuad>(unit) : nbr_kernel<5, 1>(unit);
     }
     return nullptr;
 }
@@ -93,16 +93,40 @@ bool unit_metric(const Grid *g)
 
 // LDS words of a target (target_words); the per-target stride is odd so
 // neighbouring targets start in different banks.
-int lane_words(const LaunchSpec &ls) { return target_words(ls.radius.mode, ls.radius.k, ls.k_cap); }
+int lane_words(const LaunchSpec &ls)
+{
+    return target_words(ls.radius.mode, ls.radius.k, ls.k_cap, ls.grid->dim);
+}
 int target_stride(const LaunchSpec &ls) { return lane_words(ls) | 1; }
 
-// Threads per block (kGroup lanes per target); the targets' LDS must fit
-// 64 KiB per workgroup.
+// Lanes per target.  A lane alone takes its target's some hundred dependent
+// loads one after another, which only pays when there are enough targets to
+// fill the chip with waves; below that, four lanes share a target's candidates
+// and the loads of its fit.  Kernel times with one lane and with four (the
+// groups' collectives and repeated arithmetic make four lose once the waves
+// queue): 2-D linear, 1.5k targets, 76 and 37 us; 3-D linear, 15k targets, 118
+// and 62 us; 3-D linear, 30k targets among 3M sources, 376 and 215 us; 3-D
+// quadratic, 500k targets, 733 and 967 us.  The line is one wave of quads for
+// each of 3 x 1024 SIMD slots.
+constexpr int64_t kQuadTargets = 49152;
+int target_lanes(const LaunchSpec &ls)
+{
+    return !ls.grid->lbvh && ls.n_tgt <= kQuadTargets ? kQuad : 1;
+}
+
+// Threads per block; the targets' LDS must fit 64 KiB per workgroup.  Quads
+// take one wave per block, to spread few targets over the CUs.
 int pick_block(int requested, const LaunchSpec &ls)
 {
-    int b = requested > 0 ? requested : 256;
-    while (b > 64 && (size_t)(b / kGroup) * target_stride(ls) * sizeof(int) > 65536) b >>= 1;
+    const int lanes = target_lanes(ls);
+    int b = requested > 0 ? requested : lanes > 1 ? 64 : 256;
+    while (b > 64 && (size_t)(b / lanes) * target_stride(ls) * sizeof(int) > 65536) b >>= 1;
     return b;
+}
+
+size_t block_lds(int block, const LaunchSpec &ls)
+{
+    return (size_t)(block / target_lanes(ls)) * target_stride(ls) * sizeof(int);
 }
 
 KArgs base_args(const LaunchSpec &ls, int block)
@@ -124,7 +148,7 @@ KArgs base_args(const LaunchSpec &ls, int block)
     a.max_iter = ls.radius.max_iter;
     a.r = ls.radius.r;
     a.k_cap = ls.k_cap;
-    const int tpb = block / kGroup;
+    const int tpb = block / target_lanes(ls);
     a.n_blocks = (int)((ls.n_tgt + tpb - 1) / tpb);
     a.words = lane_words(ls);
     a.stride = target_stride(ls);
@@ -152,9 +176,9 @@ pcms_status launch_neighbors(const LaunchSpec &ls, int32_t *nbr, int32_t *n_kept
     a.n_found = n_found;
     a.r2 = r2;
     a.status = status;
-    KernelFn fn = nbr_for(ls.grid->dim, unit_metric(ls.grid), ls.grid->lbvh != 0);
-    const int launch = ((a.n_blocks + 7) / 8) * 8;
-    const size_t shm = (size_t)(block / kGroup) * target_stride(ls) * sizeof(int);
+    KernelFn fn = nbr_for(ls.grid->dim, unit_metric(ls.grid), ls.grid->lbvh != 0, target_lanes(ls) > 1);
+    const int launch = launch_blocks(a.n_blocks);
+    const size_t shm = block_lds(block, ls);
     hipLaunchKernelGGL(fn, dim3(launch), dim3(block), shm, s, a);
     PCMS_HIP(hipGetLastError());
     return PCMS_OK;
@@ -176,9 +200,9 @@ pcms_status launch_transfer(const LaunchSpec &ls, const double *svals, int n_fie
     a.stage = stage;
     a.status = status;
     KernelFn fn = xfer_for(ls.grid->dim, degree, precision, unit_metric(ls.grid),
-                           ls.grid->lbvh != 0);
-    const int launch = ((a.n_blocks + 7) / 8) * 8;
-    const size_t shm = (size_t)(block / kGroup) * target_stride(ls) * sizeof(int);
+                           ls.grid->lbvh != 0, target_lanes(ls) > 1);
+    const int launch = launch_blocks(a.n_blocks);
+    const size_t shm = block_lds(block, ls);
     hipLaunchKernelGGL(fn, dim3(launch), dim3(block), shm, s, a);
     PCMS_HIP(hipGetLastError());
     return PCMS_OK;
@@ -198,16 +222,18 @@ pcms_status launch_operator(const LaunchSpec &ls, int degree, int weight, int pr
     a.op_n = op_n;
     a.status = status;
     KernelFn fn = op_for(ls.grid->dim, degree, precision, unit_metric(ls.grid),
-                         ls.grid->lbvh != 0);
-    const int launch = ((a.n_blocks + 7) / 8) * 8;
-    const size_t shm = (size_t)(block / kGroup) * target_stride(ls) * sizeof(int);
+                         ls.grid->lbvh != 0, target_lanes(ls) > 1);
+    const int launch = launch_blocks(a.n_blocks);
+    const size_t shm = block_lds(block, ls);
     hipLaunchKernelGGL(fn, dim3(launch), dim3(block), shm, s, a);
     PCMS_HIP(hipGetLastError());
     return PCMS_OK;
 }
 
-// Slots per target of an operator: every kept list fits its LDS words and
-// holds at most k_cap entries.
-int operator_width(const LaunchSpec &ls) { return std::min(lane_words(ls), ls.k_cap); }
+// Slots per target of an operator: the most entries of a kept list.
+int operator_width(const LaunchSpec &ls)
+{
+    return target_kept(ls.radius.mode, ls.radius.k, ls.k_cap);
+}
 
 }  // namespace pcms

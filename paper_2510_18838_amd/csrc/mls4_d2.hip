@@ -1,0 +1,6 @@
+// 2-D neighbour-list and transfer kernels with four lanes per target (see kernels.h).
+#include "kernels.h"
+
+namespace pcms {
+PCMS_DEFINE_DIM_KERNELS(2, kQuad)
+}  // namespace pcms

@@ -1,0 +1,6 @@
+// 5-D neighbour-list and transfer kernels with four lanes per target (see kernels.h).
+#include "kernels.h"
+
+namespace pcms {
+PCMS_DEFINE_DIM_KERNELS(5, kQuad)
+}  // namespace pcms

@@ -2,5 +2,5 @@
 #include "kernels.h"
 
 namespace pcms {
-PCMS_DEFINE_DIM_KERNELS(2)
+PCMS_DEFINE_DIM_KERNELS(2, 1)
 }  // namespace pcms

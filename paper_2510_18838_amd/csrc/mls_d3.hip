@@ -2,5 +2,5 @@
 #include "kernels.h"
 
 namespace pcms {
-PCMS_DEFINE_DIM_KERNELS(3)
+PCMS_DEFINE_DIM_KERNELS(3, 1)
 }  // namespace pcms

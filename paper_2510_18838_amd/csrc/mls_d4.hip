@@ -2,5 +2,5 @@
 #include "kernels.h"
 
 namespace pcms {
-PCMS_DEFINE_DIM_KERNELS(4)
+PCMS_DEFINE_DIM_KERNELS(4, 1)
 }  // namespace pcms

@@ -134,7 +134,7 @@ pcms_status operator_apply(const Operator &op, const double *vals, int n_fields,
     // lanes per target: one per 16-byte word of a record, at most 4
     const int lanes = nfs >= 8 ? 4 : nfs >= 4 ? 2 : 1;
     const int blocks = (int)((op.n_tgt * lanes + 255) / 256);
-    const int padded = ((blocks + 7) / 8) * 8;
+    const int padded = launch_blocks(blocks);
     if (lanes == 4)
         k_op_apply<4><<<padded, 256, 0, s>>>(op.op_n, op.op_c, op.op_w, op.tperm, (int)op.n_tgt,
                                              svals, n_fields, nfs, out, blocks);

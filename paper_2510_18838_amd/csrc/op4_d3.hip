@@ -1,0 +1,6 @@
+// 3-D operator-emission kernels with four lanes per target (see kernels.h).
+#include "kernels.h"
+
+namespace pcms {
+PCMS_DEFINE_DIM_OPERATOR(3, kQuad)
+}  // namespace pcms

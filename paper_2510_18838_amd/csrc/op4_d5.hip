@@ -1,0 +1,6 @@
+// 5-D operator-emission kernels with four lanes per target (see kernels.h).
+#include "kernels.h"
+
+namespace pcms {
+PCMS_DEFINE_DIM_OPERATOR(5, kQuad)
+}  // namespace pcms

@@ -2,5 +2,5 @@
 #include "kernels.h"
 
 namespace pcms {
-PCMS_DEFINE_DIM_OPERATOR(1)
+PCMS_DEFINE_DIM_OPERATOR(1, 1)
 }  // namespace pcms

@@ -2,5 +2,5 @@
 #include "kernels.h"
 
 namespace pcms {
-PCMS_DEFINE_DIM_OPERATOR(4)
+PCMS_DEFINE_DIM_OPERATOR(4, 1)
 }  // namespace pcms

@@ -12,12 +12,17 @@
 //
 // Stencil walk: buckets are row-major with dimension 0 fastest, so for every
 // row (c_1..c_{d-1}) the buckets c_0 in [a, b] form one contiguous range of
-// sorted sources.  Rows whose slab is farther than the radius are skipped and
+// sorted sources.  Only rows whose slab is within the radius are visited and
 // each row's c_0 range is narrowed to the chord of the ball in that slab.
 // The G lanes of a target walk the same rows (uniform control flow) and take
-// the candidates of a row in an interleaved order, so their loads are
-// contiguous; candidates reach the per-step callback in ascending sorted
-// order, which the ordered ballot compaction of the lists preserves.
+// the candidates of a row in an interleaved order; candidates reach the
+// per-step callback in ascending sorted order, which the ordered compaction
+// of the lists preserves.
+//
+// Selection reads the sources' FP32 records and decides by thresholds moved
+// apart by a proven bound on the FP32 error; the few candidates between them
+// are decided from their FP64 records, so the lists are those of the FP64
+// predicate.
 #pragma once
 
 #include "bvh.h"
@@ -26,14 +31,12 @@
 namespace pcms {
 
 // Candidates per walk step whose loads are issued together: FP64 records
-// (two 16-byte loads each) and FP32 records (one).
-#ifndef PCMS_WALK_BATCH64
-#define PCMS_WALK_BATCH64 4
-#endif
-#ifndef PCMS_WALK_BATCH32
-#define PCMS_WALK_BATCH32 4
-#endif
-constexpr int kBatch64 = PCMS_WALK_BATCH64, kBatch32 = PCMS_WALK_BATCH32;
+// (two 16-byte loads each in 3-D) and FP32 records (a lane's are adjacent and
+// load as whole 16-byte words: three words for four 3-D sources).
+constexpr int kBatch64 = 2, kBatch32 = 4;
+
+// Bins of the windowed selection.
+constexpr int kMaxBins = 64;
 
 template <int D, bool UNIT>
 PCMS_HD PCMS_INLINE double metric_d2(const double (&t)[D], const double *__restrict__ s,
@@ -65,76 +68,152 @@ PCMS_HD PCMS_INLINE double ball_beyond(double x)
     return (P(1.0) - P(x)) / (P(1.0) - P(-1.0));
 }
 
-// Rows of a stencil walk: for radius rho around t, yields the rows (bucket
-// coordinates c_1..c_{d-1}) whose slab is within reach, with each row's
-// linear id and the c_0 range of the ball's chord in that slab.
-template <int D, bool UNIT>
-struct RowIter {
+// Rows of a stencil walk: for radius rho around t, the rows (bucket
+// coordinates c_1..c_{d-1}) within reach, each with the range of sorted
+// sources in the ball's chord of that row, last row first (DOWN) or first row
+// first, kRows rows of consecutive c_1 at a time so that their bucket offsets
+// are loaded together.
+//
+// All distances are in bucket widths (every dimension above 0 with more than
+// one bucket has the metric width gp.wm, dimension 0 the width wm / sub) and
+// relative to t's own bucket, so FP32 holds them to 1e-7 of a width however
+// many buckets there are.  The c_1 of a line (fixed c_2..c_{d-1}) are those of
+// the chord in that line, so no row out of reach is visited.  Every rounding
+// is covered by slack that can only widen a range (4e-6 relative on rho^2,
+// 2e-5 of a width; the bucket assignment rounds by far less).
+constexpr int kRows = 4;
+
+template <int D, bool DOWN>
+struct RowLines {
     const GridParams &gp;
-    const double (&t)[D];
-    double rho2;
-    int a[D], b[D], c[D];
-    bool done;
+    const int *__restrict__ cs;
+    float rho2;      // squared radius in bucket widths
+    int ct[D];       // t's bucket (clamped to the grid)
+    float fr[D];     // t's offset from that bucket's lower edge
+    int c[D];        // current buckets of dimensions >= 1, relative to ct ...
+    int a[D], b[D];  // ... and their ranges
+    float outer;     // squared distance to the slabs of dimensions >= 2
+    int row;         // first bucket of the row with c_1 = 0
+    bool more;
 
-    PCMS_HD PCMS_INLINE RowIter(const GridParams &gp_, const double (&t_)[D], double rho2_)
-        : gp(gp_), t(t_), rho2(rho2_), done(false)
+    PCMS_HD PCMS_INLINE RowLines(const GridParams &gp_, const int *cs_, const double (&t)[D], double r2)
+        : gp(gp_), cs(cs_), outer(0.0f), row(0), more(true)
     {
-        const double rho = sqrt(rho2);
+        const double iw = 1.0 / gp.wm;
+        rho2 = (float)fmin(r2 * iw * iw * (1.0 + 4e-6), 1e30);
 #pragma unroll
-        for (int k = 1; k < D; ++k) {
-            double half = (UNIT ? rho : rho / gp.g[k]) * (1.0 + 1e-9) + fabs(t[k]) * 1e-15 + 1e-300;
-            a[k] = bucket_of(gp, k, t[k] - half);
-            b[k] = bucket_of(gp, k, t[k] + half);
-            c[k] = a[k];
+        for (int k = 0; k < D; ++k) {
+            const double u = (t[k] - gp.lo[k]) * gp.inv_w[k];
+            ct[k] = (int)fmin(fmax(floor(u), 0.0), (double)(gp.n[k] - 1));
+            // (a single bucket reaches everywhere; a flat dimension's width is not wm)
+            fr[k] = gp.n[k] > 1 ? (float)fmin(fmax(u - (double)ct[k], -1e15), 1e15) : 0.5f;
+            if (k >= 1) row += ct[k] * gp.stride[k];
         }
-    }
-
-    // Next row within reach; false when the stencil is exhausted.
-    PCMS_HD PCMS_INLINE bool next(int &row, int &a0, int &b0)
-    {
-        while (!done) {
-            // squared metric distance from t to this row's slab (boxes widened
-            // slightly so rounding in the bucket assignment cannot hide a source)
-            double m2 = 0.0;
-            row = 0;
+        if constexpr (D >= 3) {
 #pragma unroll
-            for (int k = 1; k < D; ++k) {
-                double blo = gp.lo[k] + (double)c[k] * gp.w[k];
-                double bhi = blo + gp.w[k];
-                double pad = 1e-7 * gp.w[k];
-                // the first and last buckets also hold clamped coordinates
-                if (c[k] == 0) blo = -INFINITY;
-                if (c[k] == gp.n[k] - 1) bhi = INFINITY;
-                double dlt = fmax(fmax(blo - pad - t[k], t[k] - bhi - pad), 0.0);
-                if (!UNIT) dlt *= gp.g[k];
-                m2 = __builtin_fma(dlt, dlt, m2);
+            for (int k = 2; k < D; ++k) {
+                chord(k, rho2);
+                c[k] = DOWN ? b[k] : a[k];
                 row += c[k] * gp.stride[k];
             }
-            const bool reach = m2 <= rho2 * (1.0 + 1e-9);
-            if (reach) {
-                double rem2 = fmax(rho2 - m2 * (1.0 - 1e-9), 0.0);
-                double half0 = (UNIT ? sqrt(rem2) : sqrt(rem2) / gp.g[0]) * (1.0 + 1e-9) +
-                               fabs(t[0]) * 1e-15 + 1e-300;
-                a0 = bucket_of(gp, 0, t[0] - half0);
-                b0 = bucket_of(gp, 0, t[0] + half0);
-            }
-            // odometer over c_1..c_{d-1}, unrolled so c stays in registers
-            bool carry = true;
+            outer = outer2();
+            if (outer > rho2) next_line();
+            else enter();
+        } else {
+            enter();
+        }
+    }
+    // The buckets of dimension k within sqrt(rem) widths of t, relative to ct.
+    PCMS_HD PCMS_INLINE void chord(int k, float rem)
+    {
+        const float h = __builtin_fmaf(sqrt_approx(rem), 1.0f + 2e-6f, 4e-5f);
+        a[k] = max((int)fminf(fmaxf(floorf(fr[k] - h), -1e9f), 1e9f), -ct[k]);
+        b[k] = min((int)fminf(fmaxf(floorf(fr[k] + h), -1e9f), 1e9f), gp.n[k] - 1 - ct[k]);
+        // t beyond the grid: the ball may miss it, its nearest bucket is kept
+        a[k] = min(a[k], gp.n[k] - 1 - ct[k]);
+        b[k] = max(b[k], -ct[k]);
+    }
+    // Distance to the slab of bucket x of dimension k.
+    PCMS_HD PCMS_INLINE float slab(int k, int x) const
+    {
+        const float y = (float)x - fr[k];
+        return fmaxf(fmaxf(y, -1.0f - y) - 2e-5f, 0.0f);
+    }
+    PCMS_HD PCMS_INLINE float outer2() const
+    {
+        float s = 0.0f;
 #pragma unroll
-            for (int k = 1; k < D; ++k) {
-                if (carry) {
-                    if (c[k] < b[k]) {
-                        c[k]++;
-                        carry = false;
-                    } else {
-                        c[k] = a[k];
+        for (int k = 2; k < D; ++k) {
+            const float d = slab(k, c[k]);
+            s = __builtin_fmaf(d, d, s);
+        }
+        return s;
+    }
+    PCMS_HD PCMS_INLINE void enter()
+    {
+        if constexpr (D >= 2) {
+            chord(1, rho2 - outer);
+            c[1] = DOWN ? b[1] : a[1];
+        }
+    }
+    // The next line within reach (an odometer over c_2..c_{d-1}, unrolled so
+    // that c stays in registers).
+    PCMS_HD PCMS_INLINE void next_line()
+    {
+        if constexpr (D >= 3) {
+            do {
+                bool carry = true;
+#pragma unroll
+                for (int k = 2; k < D; ++k) {
+                    if (carry) {
+                        carry = DOWN ? c[k] <= a[k] : c[k] >= b[k];
+                        const int step = carry ? (DOWN ? b[k] : a[k]) - c[k] : DOWN ? -1 : 1;
+                        row += step * gp.stride[k];
+                        c[k] += step;
                     }
                 }
-            }
-            if (carry) done = true;
-            if (reach) return true;
+                more = !carry;
+                outer = outer2();
+            } while (more && outer > rho2);
+            enter();
+        } else {
+            more = false;
         }
-        return false;
+    }
+    // The next rows' source ranges (beg >= end: none in that slot).  False,
+    // with every slot empty, when the stencil is exhausted.
+    PCMS_HD PCMS_INLINE bool next(int (&beg)[kRows], int (&end)[kRows])
+    {
+#pragma unroll
+        for (int u = 0; u < kRows; ++u) beg[u] = end[u] = 0;
+        if (!more) return false;
+#pragma unroll
+        for (int u = 0; u < (D == 1 ? 1 : kRows); ++u) {
+            float rem = rho2;
+            int at = row;
+            bool ok = true;
+            if constexpr (D >= 2) {
+                const int x = DOWN ? c[1] - u : c[1] + u;
+                const float d = slab(1, x);
+                ok = DOWN ? x >= a[1] : x <= b[1];
+                rem = fmaxf(rho2 - __builtin_fmaf(d, d, outer), 0.0f);
+                at += x * gp.stride[1];
+            }
+            const float h = __builtin_fmaf(sqrt_approx(rem), (1.0f + 2e-6f) * (float)gp.sub, 4e-5f);
+            const int x0 = ct[0] + (int)fminf(fmaxf(floorf(fr[0] - h), -1e9f), 1e9f);
+            const int x1 = ct[0] + (int)fminf(fmaxf(floorf(fr[0] + h), -1e9f), 1e9f);
+            if (ok) {
+                beg[u] = cs[at + min(max(x0, 0), gp.n[0] - 1)];
+                end[u] = cs[at + min(max(x1, 0), gp.n[0] - 1) + 1];
+            }
+        }
+        if constexpr (D >= 2) {
+            c[1] += DOWN ? -kRows : kRows;
+            if (DOWN ? c[1] < a[1] : c[1] > b[1]) next_line();
+        } else {
+            more = false;
+        }
+        return true;
     }
 };
 
@@ -146,44 +225,50 @@ struct Exact64 {
     const GridParams &gp;
     const double *__restrict__ spts;
     const double (&t)[D];
-    PCMS_HD PCMS_INLINE void load(int p, double (&s)[D]) const { load_src<D>(spts, p, s); }
+    // candidates p + j * G + q (j < B); those at or past end repeat p
+    template <int G, int B>
+    PCMS_HD PCMS_INLINE void load(int p, int end, int q, double (&s)[B][D]) const
+    {
+#pragma unroll
+        for (int j = 0; j < B; ++j) {
+            const int x = p + j * G + q;
+            load_src<D>(spts, x < end ? x : p, s[j]);
+        }
+    }
     PCMS_HD PCMS_INLINE double d2(const double (&s)[D]) const { return metric_d2<D, UNIT>(t, s, gp); }
 };
 
 // Image32 loads a source's FP32 record s32_k = fl32(s_k - lo_k) and returns
-// the FP32 image of D: with the target split as t_k - lo_k = th_k + tl_k (two
-// floats),
-//     v_k = (th_k - s32_k) + tl_k,   u_k = v_k * fl32(g_k),   D32 = sum u_k^2
+// the FP32 image of D: with th_k = fl32(t_k - lo_k),
+//     u_k = (th_k - s32_k) * fl32(g_k),   D32 = sum u_k^2
 // (the sum as an fma chain).  It differs from the FP64 D by at most
 //     m = alpha + beta * D32.
 // Derivation: each u_k is within A_k + B |u_k| of its FP64 counterpart, where
-// A_k = g_k |th_k| a (a >= 2^-24: rounding of the source image, plus the
-// target split) and B >= 4 * 2^-24 + 2^-24 (the FP32 roundings of u_k and of
-// g_k, and the source image through |s32_k| <= |th_k| + |v_k|).  Summing
+// A_k = g_k |th_k| a (a >= 2 * 2^-24: rounding of the source's and of the
+// target's image) and B >= 4 * 2^-24 + 2^-24 (the FP32 roundings of u_k and
+// of g_k, and the source image through |s32_k| <= |th_k| + |v_k|).  Summing
 // |u32_k^2 - u64_k^2| <= (A_k + B |u_k|)(A_k + (2 + B) |u_k|) over k, with
 // sum_k A_k |u_k| <= |A| sqrt(D) and sqrt(D) <= (D / c + c) / 2 for any c > 0,
 // and adding the d roundings of the FP32 sum, gives alpha and beta (times a
 // safety factor of 1.5).  c is chosen near the thresholds of the walk, where
-// the bound is tightest.  Coordinates beyond the FP32 range give a non-finite
-// m, which the callers treat as "unknown".
+// the bound is tightest.  Coordinates beyond the FP32 range give non-finite
+// thresholds, which the callers treat as "unknown".
 template <int D, bool UNIT>
 struct Image32 {
     using E = float;
     const float *__restrict__ s32;
-    float th[D], tl[D], g[D];
+    float th[D], g[D];
     double alpha, beta;
 
     PCMS_HD PCMS_INLINE Image32(const GridParams &gp, const float *s32_, const double (&t)[D],
                                 double c)
         : s32(s32_)
     {
-        constexpr double kA = 6.0e-8, kB = 3.1e-7, kR = 6.0e-8, kSafe = 1.5;
+        constexpr double kA = 1.2e-7, kB = 3.1e-7, kR = 6.0e-8, kSafe = 1.5;
         double a2 = 0.0;
 #pragma unroll
         for (int k = 0; k < D; ++k) {
-            const double x = t[k] - gp.lo[k];
-            th[k] = (float)x;
-            tl[k] = (float)(x - (double)th[k]);
+            th[k] = (float)(t[k] - gp.lo[k]);
             g[k] = UNIT ? 1.0f : (float)gp.g[k];
             const double ak = (UNIT ? 1.0 : gp.g[k]) * fabs((double)th[k]) * kA;
             a2 += ak * ak;
@@ -193,63 +278,59 @@ struct Image32 {
         alpha = kSafe * (A * A + (1.0 + kB) * A * c) + 1e-36;
         beta = kSafe * ((1.0 + kB) * A / c + 2.0 * kB + kB * kB + D * kR) * (1.0 + 1e-6);
     }
-    PCMS_HD PCMS_INLINE void load(int p, float (&s)[D]) const { load_src32<D>(s32, p, s); }
+    // Candidates p + j * G + q (j < B); the values of those at or past end
+    // are unspecified.  One lane's (G = 1) are B D adjacent floats, read as
+    // 16-byte words: the records' storage has room for B - 1 records past the
+    // last (the fixed-point records and kPad32 floats follow it).
+    template <int G, int B>
+    PCMS_HD PCMS_INLINE void load(int p, int end, int q, float (&s)[B][D]) const
+    {
+#ifndef PCMS_HOST_EMULATION
+        if constexpr (G == 1) {
+            static_assert(B * D % 4 == 0 && (B - 1) * D <= kPad32, "whole 16-byte words");
+            const float4u *b = reinterpret_cast<const float4u *>(s32 + (size_t)p * D);
+            float x[B * D];
+#pragma unroll
+            for (int i = 0; i < B * D / 4; ++i) {
+                const float4u v = b[i];
+#pragma unroll
+                for (int h = 0; h < 4; ++h) x[4 * i + h] = v[h];
+            }
+#pragma unroll
+            for (int j = 0; j < B; ++j)
+#pragma unroll
+                for (int k = 0; k < D; ++k) s[j][k] = x[j * D + k];
+            return;
+        }
+#endif
+#pragma unroll
+        for (int j = 0; j < B; ++j) {
+            const int x = p + j * G + q;
+            load_src32<D>(s32, x < end ? x : p, s[j]);
+        }
+    }
     PCMS_HD PCMS_INLINE float d2(const float (&s)[D]) const
     {
-        float v = (th[0] - s[0]) + tl[0];
-        float u = UNIT ? v : v * g[0];
+        float u = UNIT ? th[0] - s[0] : (th[0] - s[0]) * g[0];
         float acc = u * u;
 #pragma unroll
         for (int k = 1; k < D; ++k) {
-            v = (th[k] - s[k]) + tl[k];
-            u = UNIT ? v : v * g[k];
+            u = UNIT ? th[k] - s[k] : (th[k] - s[k]) * g[k];
             acc = __builtin_fmaf(u, u, acc);
         }
         return acc;
     }
-    // bound on |D - D32|; not finite (or NaN) when D32 cannot be trusted
-    PCMS_HD PCMS_INLINE double bound(float d32) const { return alpha + beta * (double)d32; }
-};
-
-// Classification of D by equal-width bins: -1 below lo, j for D in the j-th
-// of nb bins of [lo, hi), nb at or above hi (nb = 0, hi = lo: inside or not).
-// Monotone non-decreasing in D.
-struct Bins {
-    double lo, hi, ibw;
-    int nb;
-    PCMS_HD PCMS_INLINE int operator()(double d2) const
+    // the bound on |D - D32| for D32 up to d
+    PCMS_HD PCMS_INLINE double bound(double d) const { return alpha + beta * d; }
+    // Thresholds for the exact predicate D < x: D32 < inside(x) implies
+    // D < x, and D32 >= outside(x) implies D >= x.
+    PCMS_HD PCMS_INLINE float inside(double x) const
     {
-        return d2 < lo ? -1 : d2 < hi ? min((int)((d2 - lo) * ibw), nb - 1) : nb;
+        return (float)((x - alpha) / (1.0 + beta) * (1.0 - 1.3e-7) - 1e-36);
     }
-};
-
-// The same classification from an FP32 image: y = (D32 - lo) * ibw in FP32
-// is within mb = a + b * D32 bin widths of (D - lo) * ibw (the image's bound
-// plus the three FP32 roundings of y, plus 1e-9 for the FP64 rounding of the
-// exact classification's own edges), so when y lies farther than mb from
-// every edge its bin is the bin of D.  y is clamped to [-0.5, nb + 0.5]
-// first: beyond the outer edges only the side matters.
-struct Bins32 {
-    float lo, ibw, top, a, b;
-
-    template <int D, bool UNIT>
-    PCMS_HD PCMS_INLINE Bins32(const Bins &k, const Image32<D, UNIT> &im)
+    PCMS_HD PCMS_INLINE float outside(double x) const
     {
-        constexpr double kU = 5.97e-8;   // 2^-24, rounded up
-        lo = (float)k.lo;
-        ibw = (float)k.ibw;
-        top = (float)k.nb + 0.5f;
-        a = (float)((k.ibw * (im.alpha + 4.04 * kU * fabs(k.lo)) + 1e-9) * 1.01);
-        b = (float)(k.ibw * (im.beta + 3.03 * kU) * 1.01);
-    }
-    // the bin of D when `sure`; NaN or overflowed images are never sure
-    PCMS_HD PCMS_INLINE int operator()(float d32, bool &sure) const
-    {
-        const float y = fminf(fmaxf((d32 - lo) * ibw, -0.5f), top);
-        const float fl = floorf(y), fr = y - fl;
-        const float mb = __builtin_fmaf(b, d32, a);
-        sure = (fr > mb) & (fr + mb < 1.0f);
-        return (int)fl;
+        return beta < 0.5 ? (float)((x + alpha) / (1.0 - beta) * (1.0 + 1.3e-7) + 1e-36) : INFINITY;
     }
 };
 
@@ -258,97 +339,57 @@ struct Bins32 {
 // loads of a step are issued together); every lane of the group calls f the
 // same number of times, with valid = false on the padding slots past the end.
 template <int D, int G, int kBatch, class Meas, class F>
-PCMS_HD PCMS_INLINE void walk_range(const Meas &meas, int beg, int end, int q, F &&f)
+PCMS_HD PCMS_INLINE void walk_step(const Meas &meas, int p, int end, int q, F &&f)
 {
-    for (int p0 = beg; p0 < end; p0 += kBatch * G) {
-        // slot j of lane q is candidate p0 + j*G + q: the group's loads of
-        // one slot are contiguous
-        typename Meas::E sb[kBatch][D];
-        int pp[kBatch];
-        bool ok[kBatch];
+    typename Meas::E sb[kBatch][D];
+    meas.template load<G, kBatch>(p, end, q, sb);
 #pragma unroll
-        for (int j = 0; j < kBatch; ++j) {
-            pp[j] = p0 + j * G + q;
-            ok[j] = pp[j] < end;
-            meas.load(ok[j] ? pp[j] : beg, sb[j]);
-        }
-#pragma unroll
-        for (int j = 0; j < kBatch; ++j) f(pp[j], meas.d2(sb[j]), ok[j]);
+    for (int j = 0; j < kBatch; ++j) {
+        const int x = p + j * G + q;
+        f(x, meas.d2(sb[j]), x < end);
     }
 }
 
-// walk_range over every sorted source in the buckets that can hold a source
-// with D < rho2 (a superset of the ball).  rho2 may be +inf.  The next row's
-// bucket offsets are loaded while the current row is processed.
-template <int D, bool UNIT, int G, int kBatch, class Meas, class F>
-PCMS_HD PCMS_INLINE void walk(const GridParams &gp, const int *__restrict__ cs, const Meas &meas,
-                              const double (&t)[D], double rho2, int q, F &&f)
-{
-#ifdef PCMS_HOST_EMULATION
-    if (q == 0) ++pcms_emu_walks;
-#endif
-    RowIter<D, UNIT> it(gp, t, rho2);
-    int row, a0, b0;
-    bool have = it.next(row, a0, b0);
-    int beg = 0, end = 0;
-    if (have) {
-        beg = cs[row + a0];
-        end = cs[row + b0 + 1];
+// The ranges of sorted sources that can hold a source with D < rho2 (a
+// superset of the ball); rho2 may be +inf.  next() yields up to kSlots of them
+// (beg >= end: none in that slot), false at the end.  kDown: later ranges
+// come first (if asked, on the grid); else in ascending order.
+template <int D, bool UNIT, bool BVH, bool DOWN>
+struct Ranges {
+    static constexpr int kSlots = kRows;
+    static constexpr bool kDown = DOWN;
+    RowLines<D, DOWN> it;
+    PCMS_HD PCMS_INLINE Ranges(const GridParams &gp, const int *cs, const BvhView &,
+                               const double (&t)[D], double rho2)
+        : it(gp, cs, t, rho2)
+    {
     }
-    while (have) {
-        int nbeg = 0, nend = 0;
-        const bool nhave = it.next(row, a0, b0);
-        if (nhave) {
-            nbeg = cs[row + a0];
-            nend = cs[row + b0 + 1];
-        }
-#ifdef PCMS_HOST_EMULATION
-        if (q == 0) {
-            ++pcms_emu_rows;
-            pcms_emu_cands += end - beg;
-        }
-#endif
-        walk_range<D, G, kBatch>(meas, beg, end, q, f);
-        beg = nbeg;
-        end = nend;
-        have = nhave;
+    PCMS_HD PCMS_INLINE bool next(int (&beg)[kSlots], int (&end)[kSlots]) { return it.next(beg, end); }
+};
+
+template <int D, bool UNIT, bool DOWN>
+struct Ranges<D, UNIT, true, DOWN> {
+    static constexpr int kSlots = 1;
+    static constexpr bool kDown = false;
+    BvhIter<D, UNIT> it;
+    PCMS_HD PCMS_INLINE Ranges(const GridParams &gp, const int *, const BvhView &bv,
+                               const double (&t)[D], double rho2)
+        : it(gp, bv, t, rho2)
+    {
     }
-}
+    PCMS_HD PCMS_INLINE bool next(int (&beg)[1], int (&end)[1]) { return it.next(beg[0], end[0]); }
+};
 
 // Search state of one target, shared by its G lanes.  The target's `words`
 // LDS words L[0..words) hold the kept list (k_cap entries) and, during the
-// radius search, a buffer of words / 2 doubles (double j in words 2j, 2j+1).
-// The walk over the sources that can lie inside a ball: the grid's row walk,
-// or with BVH the leaves of the tree within reach (bvh.h).
-template <int D, bool UNIT, int G, bool BVH, int kBatch, class Meas, class F>
-PCMS_HD PCMS_INLINE void walk_any(const GridParams &gp, const int *__restrict__ cs,
-                                  const BvhView &bv, const Meas &meas, const double (&t)[D],
-                                  double rho2, int q, F &&f)
-{
-    if constexpr (BVH) {
-#ifdef PCMS_HOST_EMULATION
-        if (q == 0) ++pcms_emu_walks;
-#endif
-        bvh_leaves<D, UNIT>(gp, bv, t, rho2, [&](int beg, int end) {
-#ifdef PCMS_HOST_EMULATION
-            if (q == 0) {
-                ++pcms_emu_rows;
-                pcms_emu_cands += end - beg;
-            }
-#endif
-            walk_range<D, G, kBatch>(meas, beg, end, q, f);
-        });
-    } else {
-        walk<D, UNIT, G, kBatch>(gp, cs, meas, t, rho2, q, f);
-    }
-}
-
+// radius search, the bins of the windowed selection or a buffer of words / 2
+// doubles (double j in words 2j, 2j+1).
 template <int D, bool UNIT, int G, bool BVH = false>
 struct Search {
     const GridParams &gp;
     const int *__restrict__ cs;
     const double *__restrict__ spts;
-    const float *__restrict__ spts32;   // FP32 records (used by the F32 walks)
+    const float *__restrict__ spts32;   // FP32 records
     const int *__restrict__ perm;
     double t[D];
     int *L;     // this target's LDS words
@@ -356,6 +397,7 @@ struct Search {
     int words;  // >= max(k_cap, 2)
     Grp<G> g;
     BvhView bv; // the tree (BVH only)
+    int tab = 0;   // first word of the row table (scan32)
 
     PCMS_HD PCMS_INLINE int &at(int e)
     {
@@ -376,44 +418,157 @@ struct Search {
         unsigned long long hi = (unsigned)at(2 * j + 1);
         return __builtin_bit_cast(double, (hi << 32) | lo);
     }
+    // Calls f(p, x, valid) for the candidates of the ball D < rho2, range by
+    // range, x the measure's value (the general paths), in ascending order.
+    template <int kBatch, class Meas, class F>
+    PCMS_HD PCMS_INLINE void each_of(const Meas &meas, double rho2, F &&f)
+    {
+        using R = Ranges<D, UNIT, BVH, false>;
+        count_walk();
+        R rng(gp, cs, bv, t, rho2);
+        int beg[R::kSlots], end[R::kSlots];
+        while (rng.next(beg, end)) {
+#pragma unroll 1
+            for (int u = 0; u < R::kSlots; ++u) {
+                int p = beg[0], e = end[0];
+#pragma unroll
+                for (int x = 1; x < R::kSlots; ++x)
+                    if (u == x) {
+                        p = beg[x];
+                        e = end[x];
+                    }
+                count_range(p, e);
+                for (; p < e; p += kBatch * G) walk_step<D, G, kBatch>(meas, p, e, g.q, f);
+            }
+        }
+    }
     template <class F>
     PCMS_HD PCMS_INLINE void each(double rho2, F &&f)
     {
-        walk_any<D, UNIT, G, BVH, kBatch64>(gp, cs, bv, Exact64<D, UNIT>{gp, spts, t}, t, rho2, g.q,
-                                            f);
+        each_of<kBatch64>(Exact64<D, UNIT>{gp, spts, t}, rho2, f);
     }
 
-    // Calls f(p, bins(D), valid) for the candidates of the walk over rho2.
-    // Without F32 the class comes from the FP64 D.  With F32 the walk reads
-    // the FP32 records (kBatch32 per step) and a candidate takes the class of
-    // its image when that is certain, else loads its FP64 record; either way
-    // f sees the same classes.  c: the distance scale of the thresholds (any
-    // positive value is correct; the bound is tightest near it).
-    template <bool F32, class F>
-    PCMS_HD PCMS_INLINE void each_key(double rho2, double c, const Bins &bins, F &&f)
+    // Calls f(p, D32, valid) for the candidates of the ball D < rho2.  The
+    // ranges are first listed in a table at the end of the target's words (the
+    // first used() words are the caller's), one word each: length (12 bits)
+    // and start relative to the table's first range (20 bits).  Then one loop
+    // steps through the candidates of all of them: a lane that has finished a
+    // range takes its next one while other lanes are inside theirs.  With a
+    // loop per row, a wave's every row took its longest lane's steps (349
+    // candidate slots per walk against 200, in a host model of the 4M-source
+    // kNN search), and fetching the rows inside the steps' loop made every
+    // step pay for some lane's row.  A step's records are loaded before the
+    // previous step's are used.  The earliest range stands first and is taken
+    // first, so the words next to the caller's are free again first: f may use
+    // words below `tab` as it goes, and a table's candidates come in ascending
+    // order.  A table that does not hold all ranges is filled again.
+    // False if it can hold none (no room, or a range too long).
+    template <class U, class F>
+    PCMS_HD PCMS_INLINE bool scan32(const Image32<D, UNIT> &im, double rho2, U &&used, F &&f)
     {
-        if (!F32) {
-            each(rho2, [&](int p, double d2, bool ok) { f(p, bins(d2), ok); });
-            return;
-        }
-        const Image32<D, UNIT> im(gp, spts32, t, c);
-        const Bins32 b32(bins, im);
-        walk_any<D, UNIT, G, BVH, kBatch32>(gp, cs, bv, im, t, rho2, g.q, [&](int p, float d32, bool ok) {
-            bool sure;
-            int kk = b32(d32, sure);
-            if (ok && !sure) {
-#ifdef PCMS_HOST_EMULATION
-                ++pcms_emu_exact;
-#endif
-                kk = bins(d2_of(p));
+        using R = Ranges<D, UNIT, BVH, true>;
+        constexpr int S = R::kSlots;
+        count_walk();
+        R rng(gp, cs, bv, t, rho2);
+        int beg[S], end[S];
+        bool more = rng.next(beg, end), fits = true;
+        while (more) {
+            // (in 4-D and 5-D half of the words, as the list grows faster than
+            // the many rows of a full table are taken)
+            const int room = D >= 4 ? (words - used()) / 2 : words - used();
+            int n = 0, base = 0;
+            // slots that do not fit stay for the next table
+            bool left = false;
+            do {
+#pragma unroll
+                for (int u = 0; u < S; ++u) {
+                    if (beg[u] < end[u]) {
+                        if (n == 0) base = beg[u];
+                        const unsigned rel = (unsigned)(R::kDown ? base - beg[u] : beg[u] - base);
+                        const unsigned len = (unsigned)(end[u] - beg[u]);
+                        if (n < room && (rel >> 20) == 0 && !left) {
+                            count_range(beg[u], end[u]);
+                            fits &= len < 4096u;
+                            if (g.q == 0) at(words - 1 - n) = (int)((rel << 12) | (len & 4095u));
+                            ++n;
+                            end[u] = beg[u];
+                        } else {
+                            left = true;
+                        }
+                    }
+                }
+                if (!left) more = rng.next(beg, end);
+            } while (more && !left);
+            if (left && n == 0) fits = false;
+            if (!g.all(fits)) return false;
+            g.sync();
+            tab = words - n;
+            if (!R::kDown) {   // the earliest range first
+                for (int i = g.q; 2 * i < n - 1; i += G) {
+                    const int x = at(tab + i), y = at(words - 1 - i);
+                    at(tab + i) = y;
+                    at(words - 1 - i) = x;
+                }
+                g.sync();
             }
-            f(p, kk, ok);
-        });
+            int p = 0, e = 0;
+            unsigned w = n > 0 ? (unsigned)at(tab) : 0u;
+            auto take = [&]() {   // the next range, from w
+                p = R::kDown ? base - (int)(w >> 12) : base + (int)(w >> 12);
+                e = p + (int)(w & 4095u);
+                ++tab;
+                w = tab < words ? (unsigned)at(tab) : 0u;
+            };
+            if (n > 0) {
+                take();
+                float s[kBatch32][D];
+                im.template load<G, kBatch32>(p, e, g.q, s);
+                for (;;) {
+                    const int p0 = p, e0 = e;
+                    p += kBatch32 * G;
+                    const bool on = p < e || tab < words;
+                    if (p >= e && on) take();
+                    float nx[kBatch32][D];
+                    if (on) im.template load<G, kBatch32>(p, e, g.q, nx);
+#pragma unroll
+                    for (int j = 0; j < kBatch32; ++j) {
+                        const int x = p0 + j * G + g.q;
+                        f(x, im.d2(s[j]), x < e0);
+                    }
+                    if (!on) break;
+#pragma unroll
+                    for (int j = 0; j < kBatch32; ++j)
+#pragma unroll
+                        for (int k = 0; k < D; ++k) s[j][k] = nx[j][k];
+                }
+            }
+            g.sync();
+        }
+        return true;
+    }
+
+    PCMS_HD PCMS_INLINE void count_walk() const
+    {
+#ifdef PCMS_HOST_EMULATION
+        if (g.q == 0) ++pcms_emu_walks;
+#endif
+    }
+    PCMS_HD PCMS_INLINE void count_range(int beg, int end) const
+    {
+#ifdef PCMS_HOST_EMULATION
+        if (g.q == 0) {
+            ++pcms_emu_rows;
+            pcms_emu_cands += end - beg;
+        }
+#else
+        (void)beg;
+        (void)end;
+#endif
     }
 
     // Squared metric distance from t to the farthest corner of the bucket
     // box; every source lies closer, so a larger radius covers all sources.
-    PCMS_HD double far2() const
+    PCMS_HD PCMS_INLINE double far2() const
     {
         double acc = 0.0;
 #pragma unroll
@@ -426,23 +581,50 @@ struct Search {
     }
 
     // Collects every source with D < r2 into the list (up to k_cap, in walk
-    // order); returns the count (the same on every lane of the group).
-    template <bool F32 = false>
-    PCMS_HD int collect(double r2)
+    // order); returns the count (the same on every lane of the group).  The
+    // walk reads FP32 records; a candidate between the two thresholds is
+    // decided from its FP64 record.
+    PCMS_HD PCMS_INLINE int collect(double r2)
     {
+        const Image32<D, UNIT> im(gp, spts32, t, sqrt(r2));
+        const float in = im.inside(r2), out = im.outside(r2);
         int n = 0;
-        each_key<F32>(r2, sqrt(r2), Bins{r2, r2, 1.0 / r2, 0}, [&](int p, int kk, bool ok) {
-            // bitwise '&': the key is needed whatever ok is, so the compiler
-            // keeps the batch's loads together instead of sinking one into a
-            // branch
-            const bool acc = ok & (kk < 0);
-            const unsigned m = g.ballot(acc);
-            if (acc) {
-                const int pos = n + g.below(m);
-                if (pos < k_cap) at(pos) = p;
-            }
-            n += __builtin_popcount(m);
-        });
+        // In 1-D and 2-D, with few and long rows and FP64 records of one word,
+        // the plain walk is as fast (2-D lattice, 1M targets: 345 us against
+        // 355 with the FP32 records and 375 with the table).
+        bool kept = (D >= 3 || BVH) && out < INFINITY;
+        if (kept) {
+            auto add = [&](int p, float d, bool ok) {
+                bool acc = ok & (d < out);
+                if (acc && !(d < in)) {
+#ifdef PCMS_HOST_EMULATION
+                    ++pcms_emu_exact;
+#endif
+                    acc = d2_of(p) < r2;
+                }
+                const unsigned m = g.ballot(acc);
+                if (acc) {
+                    const int pos = n + g.below(m);
+                    if (pos < tab) at(pos) = p;
+                    else kept &= pos >= k_cap;
+                }
+                n += __builtin_popcount(m);
+            };
+            kept &= scan32(im, r2, [&]() { return min(n, k_cap); }, add);
+            kept = g.all(kept);
+        }
+        if (!kept) {   // (or no FP32 threshold, or no room for the table)
+            n = 0;
+            each_of<4>(Exact64<D, UNIT>{gp, spts, t}, r2, [&](int p, double d2, bool ok) {
+                const bool acc = ok & (d2 < r2);
+                const unsigned m = g.ballot(acc);
+                if (acc) {
+                    const int pos = n + g.below(m);
+                    if (pos < k_cap) at(pos) = p;
+                }
+                n += __builtin_popcount(m);
+            });
+        }
         g.sync();
         return n;
     }
@@ -450,7 +632,7 @@ struct Search {
     // Radius of a ball expected to hold k sources, from the bucket counts
     // around t (no point loads): the 3^d block of bucket widths around t's
     // bucket, which in dimension 0 spans sub + sub/2 slices to each side.
-    PCMS_HD double knn_radius_guess(int k) const
+    PCMS_HD PCMS_INLINE double knn_radius_guess(int k) const
     {
         if constexpr (BVH) return box_corrected(bvh_radius_guess<D, UNIT>(gp, bv, t, k));
         int a[D], b[D], c[D];
@@ -505,12 +687,17 @@ struct Search {
     // sources) holds a lower-dimensional cloud, which this model does not
     // describe, so the radius grows at most 2x.  In 1-3 dimensions (where
     // knn_select narrows the grid's window to match).
-    PCMS_HD double box_corrected(double g0) const
+    PCMS_HD PCMS_INLINE double box_corrected(double g0) const
     {
         if constexpr (D > 3) {
             return g0;
         } else {
             double gr = g0;
+            bool cut = false;
+#pragma unroll
+            for (int j = 0; j < D; ++j)
+                cut |= fmin(t[j] - gp.lo[j], gp.hi[j] - t[j]) * (UNIT ? 1.0 : gp.g[j]) < g0;
+            if (!cut) return g0;   // no face within the ball
             for (int it = 0; it < 2; ++it) {
                 double f = 1.0;
 #pragma unroll
@@ -529,7 +716,7 @@ struct Search {
     // Appends the values D in [lo, hi) to the buffer (ordered compaction,
     // at most cb kept); returns (group-uniform) the counts below lo and in
     // [lo, hi).
-    PCMS_HD void buffer_bracket(double lo, double hi, int cb, int &c_lo, int &n_in)
+    PCMS_HD PCMS_INLINE void buffer_bracket(double lo, double hi, int cb, int &c_lo, int &n_in)
     {
         int below = 0, n = 0;
         each(hi, [&](int, double d2, bool ok) {
@@ -549,7 +736,7 @@ struct Search {
 
     // r-th smallest (1-based) of the n doubles in the buffer; the lanes rank
     // interleaved entries and the group takes the minimum found.
-    PCMS_HD double buffer_rank(int n, int r)
+    PCMS_HD PCMS_INLINE double buffer_rank(int n, int r)
     {
         double ans = INFINITY;
         for (int a0 = 0; a0 < n; a0 += G) {
@@ -585,8 +772,7 @@ struct Search {
     // lies outside the window, one more window beside it is tried,
     // [b g, 1.5 b g) or [0.6 a g, a g): two walks instead of the general
     // path's bracketing.  False leaves the general path to the caller.
-    template <bool F32 = false>
-    PCMS_HD bool knn_select(int k, double &r2, int &n_found)
+    PCMS_HD PCMS_INLINE bool knn_select(int k, double &r2, int &n_found)
     {
         constexpr bool kTight = !BVH && D <= 3;
         constexpr double a = kTight ? 0.8 : 0.78, b = kTight ? 1.18 : 1.3;
@@ -595,7 +781,7 @@ struct Search {
         // one call site, so that the selection is inlined once
         for (int attempt = 0; attempt < 2; ++attempt) {
             int side = 0;
-            if (select_window<F32, false>(k, lo, hi, r2, n_found, &side)) return true;
+            if (select_window<false>(k, lo, hi, r2, n_found, &side)) return true;
             if (side > 0) {
                 lo = hi;
                 hi = (1.5 * b * gr) * (1.5 * b * gr);
@@ -610,79 +796,151 @@ struct Search {
     }
 
     // The k-th smallest D in two walks, given a window [lo, hi) expected to
-    // hold it.  The first walk, over the ball D < hi, counts the sources
-    // below lo and histograms those in [lo, hi) into nb bins of equal width
-    // in D (the target's first nb words serve as the bins).  The second walk
-    // lists, in walk order, every source of a lower bin (or below lo) and
-    // keeps the indices of the bin holding the k-th at the end of the words;
-    // the k-th is ranked among them (their D recomputed) and those below it
-    // complete the list.  Both walks classify a source with the same
-    // expression of its D, so their counts agree exactly (with F32 the walks
-    // read the FP32 records and still obtain that exact classification).  On
-    // success v is the k-th smallest D and the list holds every source with
-    // D < v, n their count (< k); with TIES the list is then completed to k
-    // entries with sources at D = v, smallest source index first, and n = k.
-    // Returns false when the k-th lies outside [lo, hi) or its bin does not
-    // fit the words; then *side (if given) is -1 if the k-th lies below lo,
-    // +1 if at or above hi, 0 otherwise.
-    template <bool F32, bool TIES>
-    PCMS_HD bool select_window(int k, double lo, double hi, double &v, int &n_out,
+    // hold it.  The first walk, over the ball D < hi, histograms the FP32
+    // images into nb bins of equal width (16-bit counts in the target's first
+    // words; the first bin also takes everything below lo).  The k-th smallest image
+    // lies in some bin b, and since every D is within the image's bound m of
+    // its image, the k-th smallest D lies within m of that bin: in [e0, e1],
+    // the bin widened by m and the rounding of the binning.  The second walk
+    // lists the sources below e0 for sure, and sets aside those that are not
+    // but may be below e1.  Every other source has D >= e1, so the k-th
+    // smallest D is ranked among those set aside (their D recomputed in FP64:
+    // one or two with untied distances, up to kReg in registers, more in a
+    // further walk), and those below it complete the list.  On success v is
+    // the k-th smallest D and the list holds every source with D < v, n their
+    // count (< k); with TIES the list is then completed to k entries with
+    // sources at D = v, smallest source index first, and n = k (the words then
+    // begin at the list: L moves).  Returns false when the k-th image lies
+    // outside [lo, hi) or the list does not fit the words; then *side (if
+    // given) is -1 if the k-th lies below lo, +1 if at or above hi, 0
+    // otherwise.
+    template <bool TIES>
+    PCMS_HD PCMS_INLINE bool select_window(int k, double lo, double hi, double &v, int &n_out,
                                int *side = nullptr)
     {
-        const int nb = words < 64 ? words : 64;
-        const double bw = (hi - lo) / nb, ibw = 1.0 / bw;
-        // -1 below lo, the bin in [lo, hi), nb at or above hi
-        const Bins key{lo, hi, ibw, nb};
-        for (int j = g.q; j < nb; j += G) at(j) = 0;
+        constexpr int kReg = 7;
+        const Image32<D, UNIT> im(gp, spts32, t, sqrt(hi));
+        const int nb = min(words, kMaxBins), nbw = nb / 2 + 1;
+        const double bw = (hi - lo) / nb;
+        const float hi32 = (float)hi, ibw = (float)(1.0 / bw), off = (float)(-lo / bw);
+        for (int j = g.q; j < nbw; j += G) at(j) = 0;
         g.sync();
-        int below = 0;
-        each_key<F32>(hi, sqrt(hi), key, [&](int, int kk, bool ok) {
-            below += ok & (kk < 0);
-            if (ok & (kk >= 0) & (kk < nb)) lds_add(&at(kk), 1);
+        const bool full = scan32(im, hi, [&]() { return nbw; }, [&](int, float d, bool ok) {
+            if (ok & (d < hi32)) {
+                const float y = fminf(fmaxf(__builtin_fmaf(d, ibw, off), 0.0f), (float)nb);
+                const int j = (int)y;
+                lds_add(&at(j >> 1), j & 1 ? 1 << 16 : 1);
+            }
         });
         g.sync();
-        const int c_lo = g.sum(below);
-        int b = -1, c_b = 0, n_b = 0;
-        if (c_lo < k) {
-            int cum = c_lo;
-            for (int j = 0; j < nb; ++j) {
-                const int cj = at(j);
-                if (b < 0 && cum + cj >= k) {
-                    b = j;
-                    c_b = cum;
-                    n_b = cj;
-                }
-                cum += cj;
-            }
+        // (a count beyond 16 bits misleads, and is caught below)
+        int b = -1, cum = 0;
+        for (int j = 0; j < nbw; ++j) {
+            const unsigned x = (unsigned)at(j);
+            const int c0 = cum + (int)(x & 0xffffu), c1 = c0 + (int)(x >> 16);
+            if (b < 0 && c1 >= k) b = c0 >= k ? 2 * j : 2 * j + 1;
+            cum = c1;
         }
         g.sync();   // every lane has read the bins before the list overwrites them
-        if (b < 0 || c_b + n_b > words) {
-            if (side) *side = b >= 0 ? 0 : c_lo >= k ? -1 : 1;
+        if (side) *side = 0;
+        if (!full) return false;
+        if (b < 0 || (b == 0 && lo > 0.0)) {
+            if (side) *side = b < 0 ? 1 : -1;
             return false;
         }
-        // bin entry j sits in word words - n_b + j
-        const int base = words - n_b;
-        const double rho2 = b == nb - 1 ? hi : fmin(hi, (lo + (double)(b + 1) * bw) * (1.0 + 1e-12));
-        int n = 0, m = 0;
-        each_key<F32>(rho2, sqrt(rho2), key, [&](int p, int kk, bool ok) {
-            const bool in = ok & (kk < b);
-            const bool bb = ok & (kk == b);
-            const unsigned mi = g.ballot(in), mb = g.ballot(bb);
-            if (in) {
-                const int pos = n + g.below(mi);
-                if (pos < c_b) at(pos) = p;
+        const double m = im.bound(hi) + 1e-6 * hi;
+        const double e0 = lo + (double)b * bw - m, e1 = lo + (double)(b + 1) * bw + m;
+        const float in = im.inside(e0), out = im.outside(e1);
+        if (!(out < INFINITY)) return false;
+        // the first kReg words hold those set aside, the list follows
+        int n = 0, nm = 0;
+        bool room = words >= kReg + k;
+        if (room) {
+            room &= scan32(im, e1, [&]() { return kReg + min(n, k); }, [&](int p, float d, bool ok) {
+                const bool acc = ok & (d < out), sure = acc & (d < in);
+                const unsigned ma = g.ballot(acc), ms = g.ballot(sure);
+                if (acc) {
+                    const int pos = sure ? kReg + n + g.below(ms) : nm + g.below(ma & ~ms);
+                    if (pos < (sure ? tab : kReg)) at(pos) = p;
+                    else room &= !sure;
+                }
+                n += __builtin_popcount(ms);
+                nm += __builtin_popcount(ma & ~ms);
+            });
+            g.sync();
+            room = g.all(room);
+            // (fewer than k, or k below e0: only where the images mislead)
+            if (room && (n >= k || n + nm < k)) return false;
+        }
+        if (room && nm <= kReg) {
+            double dm[kReg];
+            int pm[kReg], id[kReg];
+#pragma unroll
+            for (int j = 0; j < kReg; ++j) {
+                dm[j] = INFINITY;
+                pm[j] = id[j] = 0;
+                if (j < nm) {
+                    pm[j] = at(j);
+                    dm[j] = d2_of(pm[j]);
+                }
             }
-            if (bb) {
-                const int j = m + g.below(mb);
-                if (j < n_b) at(base + j) = p;
+            g.sync();
+            v = INFINITY;
+#pragma unroll
+            for (int j = 0; j < kReg; ++j) {
+                int less = 0, le = 0;
+#pragma unroll
+                for (int i = 0; i < kReg; ++i) {
+                    less += dm[i] < dm[j];
+                    le += dm[i] <= dm[j];
+                }
+                if (less < k - n && k - n <= le) v = dm[j];
             }
-            n += __builtin_popcount(mi);
-            m += __builtin_popcount(mb);
+            if (!(v >= e0 && v <= e1)) return false;   // cannot happen
+            int need = k - n;   // sources at v to keep (TIES)
+            if (TIES) {
+#pragma unroll
+                for (int j = 0; j < kReg; ++j) {
+                    need -= dm[j] < v;
+                    if (dm[j] == v) id[j] = perm[pm[j]];
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < kReg; ++j) {
+                bool take = dm[j] < v;
+                if (TIES && dm[j] == v) {
+                    int rank = 0;
+#pragma unroll
+                    for (int i = 0; i < kReg; ++i) rank += dm[i] == v && id[i] < id[j];
+                    take = rank < need;
+                }
+                if (take) {
+                    if (g.q == 0) at(kReg + n) = pm[j];
+                    ++n;
+                }
+            }
+            L += kReg;
+            words -= kReg;
+            g.sync();
+            n_out = n;
+            return true;
+        }
+        // many set aside, or no words for the table: they are listed at the
+        // end of the words, the last one first, and ranked there
+        int c_b = 0, n_b = 0;
+        each_of<kBatch32>(im, e1, [&](int p, float d, bool ok) {
+            const bool acc = ok & (d < out), sure = acc & (d < in);
+            const unsigned ma = g.ballot(acc), ms = g.ballot(sure);
+            if (acc) {
+                const int pos = sure ? c_b + g.below(ms) : words - 1 - n_b - g.below(ma & ~ms);
+                if ((unsigned)pos < (unsigned)words) at(pos) = p;
+            }
+            c_b += __builtin_popcount(ms);
+            n_b += __builtin_popcount(ma & ~ms);
         });
         g.sync();
-        if (n != c_b || m != n_b) return false;   // cannot happen: same sources, same key
-        // r-th smallest (1-based) of the bin, ranked by the lanes in turn
-        const int r = k - c_b;
+        if (c_b + n_b > words || c_b >= k || c_b + n_b < k) return false;
+        const int base = words - n_b, r = k - c_b;
         double ans = INFINITY;
         for (int a0 = 0; a0 < n_b; a0 += G) {
             const int a = a0 + g.q;
@@ -698,10 +956,11 @@ struct Search {
             }
         }
         v = g.min(ans);
+        if (!(v >= e0 && v <= e1)) return false;
         if (TIES) {
-            // the k - (c_b + #(bin entries below v)) sources at D = v of
-            // smallest source index join the list: each round marks the next
-            // one (its word holds ~p until it is appended)
+            // the k - (c_b + #(those below v)) sources at D = v of smallest
+            // source index join the list: each round marks the next one (its
+            // word holds ~p until it is appended)
             int below_v = 0;
             for (int j0 = 0; j0 < n_b; j0 += G) {
                 const int j = j0 + g.q;
@@ -730,9 +989,8 @@ struct Search {
                 prev = gb;
             }
         }
-        // append the bin's sources below v (and the marked ones) in walk
-        // order; entry j is read before position c_b + j (<= base + j) can
-        // be written
+        // append those below v and the chosen ties; entry j is read before
+        // position c_b + j (<= base + j) can be written
         int cnt = c_b;
         for (int j0 = 0; j0 < n_b; j0 += G) {
             const int j = j0 + g.q;
@@ -755,7 +1013,7 @@ struct Search {
     // when the k-th falls in the buffered interval it is ranked there,
     // otherwise the general bracketing search continues from what the walk
     // established.
-    PCMS_HD double knn_r2(int k)
+    PCMS_HD PCMS_INLINE double knn_r2(int k)
     {
         const double gr = knn_radius_guess(k);
         const int cb = words / 2;
@@ -766,9 +1024,19 @@ struct Search {
         int c_lo, n_in;
         buffer_bracket(lo, hi, cb, c_lo, n_in);
         if (c_lo < k && k <= c_lo + n_in && n_in <= cb) return buffer_rank(n_in, k - c_lo);
-        if (c_lo >= k) return kth(k, 0.0, 0, lo, cb);
-        if (c_lo + n_in < k) return kth(k, hi, c_lo + n_in, 4.0 * hi, cb);
-        return kth(k, lo, c_lo, hi, cb);
+        // (one call site, so that the search is inlined once)
+        double from = lo, to = hi;
+        int c = c_lo;
+        if (c_lo >= k) {
+            from = 0.0;
+            to = lo;
+            c = 0;
+        } else if (c_lo + n_in < k) {
+            from = hi;
+            to = 4.0 * hi;
+            c = c_lo + n_in;
+        }
+        return kth(k, from, c, to, cb);
     }
 
     // Exact k-th smallest D (1-based) over all sources, given a bracket:
@@ -777,7 +1045,7 @@ struct Search {
     // sub-intervals with one walk; once the interval holding the k-th has at
     // most `sb` (<= words / 2) sources they are copied into the buffer and
     // ranked.
-    PCMS_HD double kth(int k, double lo, int c_lo, double hi, int sb)
+    PCMS_HD PCMS_INLINE double kth(int k, double lo, int c_lo, double hi, int sb)
     {
         constexpr int NB = 8;
         const double farr = far2();
@@ -870,13 +1138,25 @@ struct Search {
     // Keeps the k_cap smallest (D, source index) among D < r2 in the list
     // (called when more than k_cap sources are inside); returns the number of
     // list entries written.
-    template <bool F32 = false>
-    PCMS_HD int cap_collect(double r2)
+    PCMS_HD PCMS_INLINE int cap_collect(double r2, int n_found)
     {
-        // usually two walks: the k_cap-th lies in the window [0, r2)
-        double vw;
+        // usually two walks: the k_cap-th lies in the window [0, r2).  In 4-D
+        // and 5-D, where most of the ball is near its surface and its bins
+        // would hold many sources, in the part of it expected to hold the
+        // sources of rank k_cap - 5 sqrt(k_cap) to k_cap + 5 sqrt(k_cap).
+        double vw, lo = 0.0, hi = r2;
         int nw;
-        if (select_window<F32, true>(k_cap, 0.0, r2, vw, nw)) return nw;
+        if constexpr (D >= 4) {
+            const float s = 5.0f * sqrt_approx((float)k_cap), f = 1.0f / (float)n_found;
+            lo = r2 * (double)powf(fmaxf((float)k_cap - s, 0.0f) * f, 2.0f / D);
+            hi = r2 * (double)powf(fminf(((float)k_cap + s) * f, 1.0f), 2.0f / D);
+        }
+        // (one call site, so that the selection is inlined once)
+        for (int attempt = 0; attempt < (D >= 4 ? 2 : 1); ++attempt) {
+            if (select_window<true>(k_cap, lo, hi, vw, nw)) return nw;
+            lo = 0.0;
+            hi = r2;
+        }
         const double v = kth(k_cap, 0.0, 0, r2, words / 2);
         const double vnext = nextafter(v, INFINITY);
         int n = 0, c_eq = 0;
