@@ -375,7 +375,6 @@ pcms_status batch_setup(BatchPlan &p)
     const size_t o_v0 = take(sizeof(int) * nmax);
     const size_t o_v1 = take(sizeof(int) * nmax);
     const size_t o_hist = take(sizeof(int) * sort_hist_ints((int)nmax));
-    const size_t o_scan = take(sizeof(int) * sort_scan_ints((int)nmax));
     const size_t o_cs = take(sizeof(int) * cs);
     const size_t o_perm = take(sizeof(int) * src);
     const size_t o_iperm = take(sizeof(int) * src);
@@ -402,7 +401,6 @@ pcms_status batch_setup(BatchPlan &p)
     p.v0 = (int *)(w + o_v0);
     p.v1 = (int *)(w + o_v1);
     p.hist = (int *)(w + o_hist);
-    p.scan = (int *)(w + o_scan);
     p.cs = (int *)(w + o_cs);
     p.perm = (int *)(w + o_perm);
     p.iperm = (int *)(w + o_iperm);
@@ -466,7 +464,7 @@ pcms_status batch_enqueue(BatchPlan &p, hipStream_t s)
                                                                p.k0, p.v0);
     PCMS_HIP(hipGetLastError());
     pcms_status st = sort_pairs(p.k0, p.v0, p.k1, p.v1, (int)p.n_src_tot, p.key_bits, p.hist,
-                                p.scan, s);
+                                s);
     if (st != PCMS_OK) return st;
     k_batch_cell_start<<<grid_for(p.cs_tot, tpb), tpb, 0, s>>>(p.probs_d, p.params, p.cs_pref, n,
                                                               p.k0, p.cs);
@@ -482,7 +480,7 @@ pcms_status batch_enqueue(BatchPlan &p, hipStream_t s)
         k_batch_tgt_keys<<<grid_for(p.n_tgt_tot, tpb), tpb, 0, s>>>(p.probs_d, p.params, p.tgt_pref,
                                                                    n, p.k0, p.v0);
         PCMS_HIP(hipGetLastError());
-        st = sort_pairs(p.k0, p.v0, p.k1, p.v1, (int)p.n_tgt_tot, p.tkey_bits, p.hist, p.scan, s);
+        st = sort_pairs(p.k0, p.v0, p.k1, p.v1, (int)p.n_tgt_tot, p.tkey_bits, p.hist, s);
         if (st != PCMS_OK) return st;
         k_batch_tperm<<<grid_for(p.n_tgt_tot, tpb), tpb, 0, s>>>(p.tgt_pref, n, p.v0, p.tperm);
         PCMS_HIP(hipGetLastError());

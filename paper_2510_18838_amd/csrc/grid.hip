@@ -208,77 +208,133 @@ k_digit_hist(const unsigned *__restrict__ keys, int n, int shift, int *__restric
     hist[threadIdx.x * nb + blockIdx.x] = h[threadIdx.x];   // digit-major
 }
 
-// One block's kSortItems keys: each is ranked within its digit in block
-// order (the wave multisplit of every round against the block's running
-// digit counts), placed digit-sorted in LDS, and then written out so that
-// consecutive threads store consecutive slots of one digit's run (the run
-// starts at the block's global offset for the digit).  Writing straight
-// from the rounds stored every key to an isolated slot; the reorder makes
-// the stores whole segments.  Stable: a digit's keys keep their block order,
-// and the blocks their order through the digit-major offsets.
+// Inclusive prefix sums of each digit's block counts, in place (block d scans
+// row d of hist; the row's last entry is the digit's total).
+__global__ void __launch_bounds__(kScanThreads)
+k_digit_scan(int *__restrict__ hist, int nb)
+{
+    __shared__ int s[kScanThreads];
+    const int t = threadIdx.x;
+    int *row = hist + (size_t)blockIdx.x * nb;
+    const int per = (nb + kScanThreads - 1) / kScanThreads;
+    const int beg = min(t * per, nb), end = min(beg + per, nb);
+    int local = 0;
+    for (int i = beg; i < end; ++i) local += row[i];
+    s[t] = local;
+    __syncthreads();
+    for (int off = 1; off < kScanThreads; off <<= 1) {
+        const int x = t >= off ? s[t - off] : 0;
+        __syncthreads();
+        s[t] += x;
+        __syncthreads();
+    }
+    int run = s[t] - local;
+    for (int i = beg; i < end; ++i) {
+        run += row[i];
+        row[i] = run;
+    }
+}
+
+// Block-wide exclusive scan of one int per digit (256 threads); s: 256 ints.
+__device__ __forceinline__ int scan_digits(int c, int *s)
+{
+    const int t = threadIdx.x;
+    s[t] = c;
+    __syncthreads();
+    for (int off = 1; off < 256; off <<= 1) {
+        const int x = t >= off ? s[t - off] : 0;
+        __syncthreads();
+        s[t] += x;
+        __syncthreads();
+    }
+    return s[t] - c;
+}
+
+// One block's kSortItems keys, each wave ranking its own quarter of them: the
+// rank of a key among its digit's in the quarter is the wave's running count
+// of the digit plus the earlier lanes of the round (wave multisplit), with no
+// barrier between the rounds.  The keys are then placed digit-sorted in LDS
+// and written out so that consecutive threads store consecutive slots of one
+// digit's run.  Stable: a digit's keys keep their order in a quarter, the
+// quarters theirs through the waves' prefix, the blocks theirs through hist.
+// The block's global offset for a digit is its prefix among the blocks
+// (DIRECT: summed here from the other blocks' counts, for few blocks; else
+// k_digit_scan's) plus the totals of the digits below.  12.5 us for 1M keys
+// (24 MB: 1.9 TB/s; 245 blocks leave the chip short of waves); with four
+// barriers in each of 16 rounds it was 24 us, and three scan launches of 4.6 us
+// each stood in k_digit_scan's place.
+template <bool DIRECT>
 __global__ void __launch_bounds__(kSortThreads)
 k_digit_scatter(const unsigned *__restrict__ kin, const int *__restrict__ vin, int n, int shift,
-                const int *__restrict__ offs, int nb, unsigned *__restrict__ kout,
+                const int *__restrict__ hist, int nb, unsigned *__restrict__ kout,
                 int *__restrict__ vout)
 {
-    __shared__ int running[256];
-    __shared__ int wave_cnt[4][256];
-    __shared__ int lstart[257];
+    __shared__ int cnt[4][256];
+    __shared__ int lstart[256], gstart[256], scan[256];
     __shared__ unsigned skey[kSortItems];
     __shared__ int sval[kSortItems];
-    const int t = threadIdx.x;
-    const int w = t >> 6;
-    const int lane = t & 63;
-    running[t] = 0;
+    const int t = threadIdx.x, w = t >> 6, lane = t & 63;
     const int base = blockIdx.x * kSortItems;
+    const int first = base + w * (kSortItems / 4) + lane;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) cnt[v][t] = 0;
     unsigned key_r[kSortRounds];
-    int val_r[kSortRounds], lpos_r[kSortRounds];
+    int val_r[kSortRounds], pos_r[kSortRounds];
 #pragma unroll
     for (int r = 0; r < kSortRounds; ++r) {
-        lpos_r[r] = -1;
-        key_r[r] = 0u;
-        val_r[r] = 0;
-        if (base + r * kSortThreads >= n) continue;      // uniform across the block
-        const int i = base + r * kSortThreads + t;
-        const bool valid = i < n;
-        const unsigned key = valid ? kin[i] : 0u;
-        const int val = valid ? vin[i] : 0;
-        const int digit = (key >> shift) & 255;
+        const int i = first + r * 64;
+        key_r[r] = i < n ? kin[i] : 0u;
+        val_r[r] = i < n ? vin[i] : 0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kSortRounds; ++r) {
+        const bool valid = first + r * 64 < n;
+        const int digit = (key_r[r] >> shift) & 255;
         unsigned long long bits[8];
 #pragma unroll
         for (int b = 0; b < 8; ++b) bits[b] = __ballot((digit >> b) & 1);
         const unsigned long long mask = digit_match(__ballot(valid), bits, digit);
-        wave_cnt[0][t] = 0;
-        wave_cnt[1][t] = 0;
-        wave_cnt[2][t] = 0;
-        wave_cnt[3][t] = 0;
-        __syncthreads();
-        if (valid && (mask & lanes_below(lane)) == 0) wave_cnt[w][digit] = __popcll(mask);
-        __syncthreads();
-        if (valid) {
-            lpos_r[r] = scatter_slot(running[digit], wave_cnt, w, digit, mask, lane);
-            key_r[r] = key;
-            val_r[r] = val;
-        }
-        __syncthreads();
-        running[t] += wave_cnt[0][t] + wave_cnt[1][t] + wave_cnt[2][t] + wave_cnt[3][t];
-        __syncthreads();
+        const int rank = __popcll(mask & lanes_below(lane));
+        // one wave's LDS accesses are ordered: every lane reads the count
+        // before the digit's first lane raises it
+        pos_r[r] = cnt[w][digit] + rank;
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        if (valid && rank == 0) cnt[w][digit] += __popcll(mask);
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     }
-    // lstart = exclusive scan of the block's digit counts (Hillis-Steele)
-    int c = running[t];
-    lstart[t + 1] = c;
-    if (t == 0) lstart[0] = 0;
     __syncthreads();
-    for (int off = 1; off < 256; off <<= 1) {
-        const int x = t >= off ? lstart[t + 1 - off] : 0;
-        __syncthreads();
-        lstart[t + 1] += x;
-        __syncthreads();
+    // digit t: the waves' offsets in its run, the run's start in the block,
+    // and its global offset less that start
+    int run = 0;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int c = cnt[v][t];
+        cnt[v][t] = run;
+        run += c;
     }
+    const int start = scan_digits(run, scan);
+    lstart[t] = start;
+    int total, before = 0;
+    if (DIRECT) {
+        total = 0;
+        for (int b = 0; b < nb; ++b) {
+            const int c = hist[t * nb + b];
+            before += b < (int)blockIdx.x ? c : 0;
+            total += c;
+        }
+    } else {
+        total = hist[t * nb + nb - 1];
+        if (blockIdx.x > 0) before = hist[t * nb + blockIdx.x - 1];
+    }
+    __syncthreads();
+    gstart[t] = scan_digits(total, scan) + before - start;
+    __syncthreads();
 #pragma unroll
     for (int r = 0; r < kSortRounds; ++r) {
-        if (lpos_r[r] >= 0) {
-            const int p = lstart[(key_r[r] >> shift) & 255] + lpos_r[r];
+        if (first + r * 64 < n) {
+            const int digit = (key_r[r] >> shift) & 255;
+            const int p = lstart[digit] + cnt[w][digit] + pos_r[r];
             skey[p] = key_r[r];
             sval[p] = val_r[r];
         }
@@ -287,8 +343,7 @@ k_digit_scatter(const unsigned *__restrict__ kin, const int *__restrict__ vin, i
     const int nvalid = min(kSortItems, n - base);
     for (int j = t; j < nvalid; j += kSortThreads) {
         const unsigned key = skey[j];
-        const int d = (key >> shift) & 255;
-        const int pos = offs[d * nb + blockIdx.x] + (j - lstart[d]);
+        const int pos = gstart[(key >> shift) & 255] + j;
         kout[pos] = key;
         vout[pos] = sval[j];
     }
@@ -363,10 +418,15 @@ int key_bits(int n_cells_cap)
     return b;
 }
 
+// Blocks up to which a scatter sums the other blocks' counts itself: one
+// launch less per pass, for 256 nb more reads per block.
+constexpr int kDirectBlocks = 32;
+
 // Sorts (keys, vals) stably by key bits [lo_bit, bits); the result ends up
-// in (k0, v0).
+// in (k0, v0).  Per pass a histogram, a scan for more than kDirectBlocks
+// blocks, and a scatter.
 pcms_status radix_sort(unsigned *k0, int *v0, unsigned *k1, int *v1, int n, int bits, int *hist,
-                       int *scan_scratch, hipStream_t s, int lo_bit = 0)
+                       hipStream_t s, int lo_bit = 0)
 {
     int nb = (n + kSortItems - 1) / kSortItems;
     if (nb == 0) return PCMS_OK;
@@ -377,9 +437,15 @@ pcms_status radix_sort(unsigned *k0, int *v0, unsigned *k1, int *v1, int n, int 
         int shift = lo_bit + 8 * ps;
         k_digit_hist<<<nb, kSortThreads, 0, s>>>(kin, n, shift, hist, nb);
         PCMS_HIP(hipGetLastError());
-        pcms_status st = scan_exclusive(hist, 256 * nb, scan_scratch, s);
-        if (st != PCMS_OK) return st;
-        k_digit_scatter<<<nb, kSortThreads, 0, s>>>(kin, vin, n, shift, hist, nb, kout, vout);
+        if (nb <= kDirectBlocks) {
+            k_digit_scatter<true><<<nb, kSortThreads, 0, s>>>(kin, vin, n, shift, hist, nb, kout,
+                                                              vout);
+        } else {
+            k_digit_scan<<<256, kScanThreads, 0, s>>>(hist, nb);
+            PCMS_HIP(hipGetLastError());
+            k_digit_scatter<false><<<nb, kSortThreads, 0, s>>>(kin, vin, n, shift, hist, nb, kout,
+                                                               vout);
+        }
         PCMS_HIP(hipGetLastError());
         std::swap(kin, kout);
         std::swap(vin, vout);
@@ -394,6 +460,8 @@ pcms_status radix_sort(unsigned *k0, int *v0, unsigned *k1, int *v1, int n, int 
 size_t sort_scratch_bytes(int n)
 {
     int nb = (n + kSortItems - 1) / kSortItems;
+    // (the second term is spare: the size, which bounds the calls the
+    // allocation-free entry point takes, is kept)
     size_t ints = (size_t)256 * nb + (size_t)scan_scratch_ints(256 * nb);
     return sizeof(unsigned) * 2 * (size_t)n + sizeof(int) * 2 * (size_t)n + sizeof(int) * ints + 256;
 }
@@ -582,17 +650,14 @@ pcms_status build_grid_device(Grid *grid, const double *src, double cell_width,
     cur += sizeof(unsigned) * (size_t)n;
     int *v1 = (int *)cur;
     cur += sizeof(int) * (size_t)n;
-    int nb = (n + kSortItems - 1) / kSortItems;
     int *hist = (int *)cur;
-    cur += sizeof(int) * (size_t)256 * nb;
-    int *scan_scratch = (int *)cur;
 
     if ((st = source_bbox_params(grid, src, gdev, bb, cell_width, pts_per_cell, s)) != PCMS_OK)
         return st;
     if (after_params && (st = (*after_params)()) != PCMS_OK) return st;
     if ((st = bucket_keys(grid->dim, grid->params, src, n, k0, grid->perm, grid_blocks(n, 256), s)) != PCMS_OK)
         return st;
-    st = radix_sort(k0, grid->perm, k1, v1, n, key_bits(grid->n_cells_cap), hist, scan_scratch, s);
+    st = radix_sort(k0, grid->perm, k1, v1, n, key_bits(grid->n_cells_cap), hist, s);
     if (st != PCMS_OK) return st;
     k_cell_start<<<(unsigned)(((int64_t)n + kCellStartBlock) / kCellStartBlock), kCellStartBlock, 0,
                    s>>>(grid->params, k0, n, grid->cell_start);
@@ -621,10 +686,7 @@ pcms_status sort_targets(const Grid *grid, const double *tgt, int64_t n_tgt, int
     cur += sizeof(unsigned) * (size_t)n;
     int *v1 = (int *)cur;
     cur += sizeof(int) * (size_t)n;
-    int nb = (n + kSortItems - 1) / kSortItems;
     int *hist = (int *)cur;
-    cur += sizeof(int) * (size_t)256 * nb;
-    int *scan_scratch = (int *)cur;
     // tiled Morton order when its keys fit 32 bits, else bucket order; on an
     // LBVH (one bucket) the Morton order of the tree's box
     const double bound = tile_key_bound((double)grid->n_cells_cap, grid->dim);
@@ -652,7 +714,7 @@ pcms_status sort_targets(const Grid *grid, const double *tgt, int64_t n_tgt, int
     // only the key's top target_key_bits() bits are sorted on: the order is
     // for locality (a wave's targets close together), and the lowest bits
     // of the finest keys buy no measurable locality for their extra pass
-    st = radix_sort(k0, tperm, k1, v1, n, bits, hist, scan_scratch, s,
+    st = radix_sort(k0, tperm, k1, v1, n, bits, hist, s,
                     std::max(bits - target_key_bits(), 0));
     if (st != PCMS_OK) return st;
     if (raw) scratch_free(raw, s);
@@ -667,9 +729,9 @@ int target_key_bits()
 }
 
 pcms_status sort_pairs(unsigned *k0, int *v0, unsigned *k1, int *v1, int n, int bits, int *hist,
-                       int *scan_scratch, hipStream_t s)
+                       hipStream_t s)
 {
-    return radix_sort(k0, v0, k1, v1, n, bits, hist, scan_scratch, s);
+    return radix_sort(k0, v0, k1, v1, n, bits, hist, s);
 }
 
 pcms_status exclusive_scan(int *data, int n, int *scratch, hipStream_t s)
@@ -680,8 +742,6 @@ pcms_status exclusive_scan(int *data, int n, int *scratch, hipStream_t s)
 size_t exclusive_scan_ints(int n) { return (size_t)scan_scratch_ints(n); }
 
 size_t sort_hist_ints(int n) { return (size_t)256 * ((n + kSortItems - 1) / kSortItems); }
-
-size_t sort_scan_ints(int n) { return (size_t)scan_scratch_ints((int)sort_hist_ints(n)); }
 
 int bits_for(double bound)
 {

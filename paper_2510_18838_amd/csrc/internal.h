@@ -102,12 +102,11 @@ pcms_status gather_values(const Grid *grid, const double *vals, int n_fields, do
                           hipStream_t s);
 
 // Stable LSD radix sort of (key, value) pairs by the low `bits` key bits; the
-// result ends in (k0, v0).  hist and scan_scratch hold sort_hist_ints(n) and
-// sort_scan_ints(n) ints.  Enqueues kernels and device copies only.
+// result ends in (k0, v0).  hist holds sort_hist_ints(n) ints.  Enqueues
+// kernels and device copies only.
 pcms_status sort_pairs(unsigned *k0, int *v0, unsigned *k1, int *v1, int n, int bits, int *hist,
-                       int *scan_scratch, hipStream_t s);
+                       hipStream_t s);
 size_t sort_hist_ints(int n);
-size_t sort_scan_ints(int n);
 // Smallest b <= 32 with 2^b >= bound.
 int bits_for(double bound);
 
@@ -178,6 +177,7 @@ pcms_status zero_ints(int32_t *p, int n, hipStream_t s);
 struct Operator {
     int64_t n_src = 0, n_tgt = 0;
     int width = 0;
+    int device = 0;
     void *mem = nullptr;      // one allocation holding the arrays below
     int *tperm = nullptr;
     int *perm = nullptr;
@@ -240,7 +240,7 @@ struct BatchPlan {
     long long *bb = nullptr;          // [n][2][kMaxDim] ordered min/max keys
     int64_t *src_pref = nullptr, *tgt_pref = nullptr, *cs_pref = nullptr;   // [n + 1]
     unsigned *k0 = nullptr, *k1 = nullptr;
-    int *v0 = nullptr, *v1 = nullptr, *hist = nullptr, *scan = nullptr;
+    int *v0 = nullptr, *v1 = nullptr, *hist = nullptr;
     int *cs = nullptr, *perm = nullptr, *iperm = nullptr, *tperm = nullptr;
     double *spts = nullptr, *svals = nullptr;
     float *spts32 = nullptr;

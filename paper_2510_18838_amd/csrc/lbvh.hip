@@ -336,8 +336,6 @@ pcms_status build_lbvh_device(Grid *g, const double *src, int max_leaf, hipStrea
     cur += sizeof(int) * (size_t)n;
     int *hist = (int *)cur;
     cur += sizeof(int) * sort_hist_ints(n);
-    int *scan_scratch = (int *)cur;
-    cur += sizeof(int) * sort_scan_ints(n);
     cur = (char *)(((uintptr_t)cur + 255) & ~(uintptr_t)255);
     const TreeScratch w((int *)cur, n);
     g->lbvh = 1;   // before after_params: work forked there orders targets by Morton code
@@ -345,7 +343,7 @@ pcms_status build_lbvh_device(Grid *g, const double *src, int max_leaf, hipStrea
     if ((st = source_bbox_params(g, src, gdev, bb, 0.0, (double)n, s)) != PCMS_OK) return st;
     if (after_params && (st = (*after_params)()) != PCMS_OK) return st;
     if ((st = morton_keys(dim, g->params, src, n, k0, g->perm, s)) != PCMS_OK) return st;
-    if ((st = sort_pairs(k0, g->perm, k1, v1, n, 32, hist, scan_scratch, s)) != PCMS_OK) return st;
+    if ((st = sort_pairs(k0, g->perm, k1, v1, n, 32, hist, s)) != PCMS_OK) return st;
     k_single_cell<<<1, 64, 0, s>>>(n, g->cell_start);
     PCMS_HIP(hipGetLastError());
     if ((st = gather_records(g, src, s)) != PCMS_OK) return st;
