@@ -43,6 +43,18 @@ __device__ __forceinline__ int segment_of(const int64_t *__restrict__ pref, int 
     return lo;
 }
 
+// The same for the threads of a block whose first index is `base`: one search
+// for the block (its loads are uniform), then few steps, as 256 consecutive
+// indices rarely span problems.  A search per thread cost the field records of
+// 512 problems (11M sources, 8.5 fields) half of their 1.4 ms.
+__device__ __forceinline__ int segment_from(const int64_t *__restrict__ pref, int n, int64_t base,
+                                            int64_t j)
+{
+    int q = segment_of(pref, n, base);
+    while (q + 1 < n && pref[q + 1] <= j) ++q;
+    return q;
+}
+
 __device__ inline long long ordered_key(double x)
 {
     long long b = __double_as_longlong(x);
@@ -162,7 +174,7 @@ __global__ void k_batch_src_keys(const BatchProb *__restrict__ probs,
     const int64_t total = pref[n];
     for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < total;
          j += (int64_t)gridDim.x * blockDim.x) {
-        const int q = segment_of(pref, n, j);
+        const int q = segment_from(pref, n, j - threadIdx.x, j);
         const BatchProb &P = probs[q];
         const double *x = P.src + (j - P.src_off) * P.dim;
         keys[j] = P.key_off + bucket_key(params[q], x);
@@ -181,7 +193,7 @@ __global__ void k_batch_cell_start(const BatchProb *__restrict__ probs,
     const int64_t total = cs_pref[n];
     for (int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; c < total;
          c += (int64_t)gridDim.x * blockDim.x) {
-        const int q = segment_of(cs_pref, n, c);
+        const int q = segment_from(cs_pref, n, c - threadIdx.x, c);
         const BatchProb &P = probs[q];
         const int cl = (int)(c - cs_pref[q]);
         if (cl > params[q].n_cells) {
@@ -210,7 +222,7 @@ __global__ void k_batch_gather_pts(const BatchProb *__restrict__ probs,
     const int64_t total = pref[n];
     for (int64_t P0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; P0 < total;
          P0 += (int64_t)gridDim.x * blockDim.x) {
-        const int q = segment_of(pref, n, P0);
+        const int q = segment_from(pref, n, P0 - threadIdx.x, P0);
         const BatchProb &B = probs[q];
         const int p = (int)(P0 - B.src_off);
         const int jl = (int)(sorted_vals[P0] - B.src_off);
@@ -230,14 +242,22 @@ __global__ void k_batch_scatter_vals(const BatchProb *__restrict__ probs,
     const int64_t total = pref[n];
     for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < total;
          j += (int64_t)gridDim.x * blockDim.x) {
-        const int q = segment_of(pref, n, j);
+        const int q = segment_from(pref, n, j - threadIdx.x, j);
         const BatchProb &B = probs[q];
         const int64_t jl = j - B.src_off;
         double *row = svals + B.sval_off + (int64_t)iperm[j] * B.nfs;
-        // whole 16-byte words (the records are 16-byte aligned)
-        for (int l = 0; l < B.nfs; l += 2) {
-            const double a = B.vals[(int64_t)l * B.n_src + jl];
-            const double b = l + 1 < B.nf ? B.vals[(int64_t)(l + 1) * B.n_src + jl] : 0.0;
+        // whole 16-byte words (the records are 16-byte aligned), four fields'
+        // loads at once
+        const int64_t ns = B.n_src;
+        const double *v = B.vals + jl;
+        int l = 0;
+        for (; l + 4 <= B.nf; l += 4) {
+            const double a = v[l * ns], b = v[(l + 1) * ns], c = v[(l + 2) * ns], d = v[(l + 3) * ns];
+            *reinterpret_cast<double2 *>(row + l) = make_double2(a, b);
+            *reinterpret_cast<double2 *>(row + l + 2) = make_double2(c, d);
+        }
+        for (; l < B.nfs; l += 2) {
+            const double a = v[l * ns], b = l + 1 < B.nf ? v[(l + 1) * ns] : 0.0;
             *reinterpret_cast<double2 *>(row + l) = make_double2(a, b);
         }
     }
@@ -252,7 +272,7 @@ __global__ void k_batch_tgt_keys(const BatchProb *__restrict__ probs,
     const int64_t total = pref[n];
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < total;
          i += (int64_t)gridDim.x * blockDim.x) {
-        const int q = segment_of(pref, n, i);
+        const int q = segment_from(pref, n, i - threadIdx.x, i);
         const BatchProb &P = probs[q];
         const double *x = P.tgt + (i - P.tgt_off) * P.dim;
         keys[i] = P.tkey_off + (P.tiled ? target_key(params[q], x) : bucket_key(params[q], x));
@@ -267,7 +287,7 @@ __global__ void k_batch_tperm(const int64_t *__restrict__ pref, int n,
     const int64_t total = pref[n];
     for (int64_t I = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; I < total;
          I += (int64_t)gridDim.x * blockDim.x) {
-        const int q = segment_of(pref, n, I);
+        const int q = segment_from(pref, n, I - threadIdx.x, I);
         tperm[I] = (int)(sorted_vals[I] - pref[q]);
     }
 }
@@ -304,7 +324,6 @@ pcms_status batch_setup(BatchPlan &p)
         sv += (int64_t)B.n_src * B.nfs;
         keys += (double)B.cells_cap;
         tkeys += tile_key_bound((double)B.cells_cap, B.dim);
-        p.max_stride = std::max(p.max_stride, B.stride);
     }
     if (src >= ((int64_t)1 << 31) || tgt >= ((int64_t)1 << 31) || keys >= 4294967295.0) {
         set_error("batch too large: total sources and targets must stay below 2^31");
@@ -352,6 +371,12 @@ pcms_status batch_setup(BatchPlan &p)
     std::vector<int4> sorted(items.size());
     for (size_t i = 0; i < order.size(); ++i) sorted[i] = items[order[i]];
     p.n_items = (int)sorted.size();
+    p.cls_stride.assign(kBatchClasses, 1);
+    for (const BatchProb &B : p.hp)
+        if (B.dim <= 3) {
+            int &w = p.cls_stride[batch_class(B.dim, B.degree, B.unit)];
+            w = std::max(w, B.stride);
+        }
     p.cls_begin.assign(kBatchClasses, 0);
     p.cls_end.assign(kBatchClasses, 0);
     for (size_t i = order.size(); i-- > 0;) p.cls_begin[cls[order[i]]] = (int)i;
@@ -500,10 +525,12 @@ pcms_status batch_enqueue(BatchPlan &p, hipStream_t s)
         b.summary = p.summary;
         b.weight = p.weight;
         b.lambda = p.lambda;
-        const size_t shm = (size_t)p.block * p.max_stride * sizeof(int);
         // one launch per class present, in class order
         for (int c = 0; c < kBatchClasses; ++c) {
             if (p.cls_end[c] <= p.cls_begin[c]) continue;
+            // each class takes the LDS of its own problems: the linear ones of
+            // a mixed batch need half of what the quadratic ones do
+            const size_t shm = (size_t)p.block * p.cls_stride[c] * sizeof(int);
             b.item_begin = p.cls_begin[c];
             b.item_end = p.cls_end[c];
             st = p.precision == PCMS_FP64  ? batch_launch<PCMS_FP64>(c, b, p.block, shm, s)

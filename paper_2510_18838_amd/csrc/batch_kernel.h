@@ -41,9 +41,14 @@ struct BArgs {
 template <int PREC>
 pcms_status batch_launch(int cls, const BArgs &b, int block, size_t shm, hipStream_t s);
 
-#ifndef PCMS_BATCH_WAVES
-#define PCMS_BATCH_WAVES(PREC) ((PREC) == PCMS_MIXED_REFINE ? 2 : 3)
-#endif
+// Waves per SIMD the register allocator targets: two where MIXED_REFINE spills
+// under three and the lists' LDS leaves no more anyway (3-D quadratic), else
+// three.
+template <int PREC, int D, int P>
+constexpr int batch_waves()
+{
+    return PREC == PCMS_MIXED_REFINE && D == 3 && P == 2 ? 2 : 3;
+}
 
 namespace {
 
@@ -57,7 +62,7 @@ namespace {
 // kept the per-target state of one item live across the loop and spilled
 // 200-290 bytes per lane.)
 template <int PREC, int D, int P, bool UNIT>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PCMS_BATCH_WAVES(PREC))))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(batch_waves<PREC, D, P>())))
 k_batch_transfer(BArgs b)
 {
     extern __shared__ int lds[];

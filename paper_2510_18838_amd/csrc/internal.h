@@ -233,7 +233,7 @@ struct BatchPlan {
     int weight = 0, precision = 0, block = 256;
     double lambda = 0.0, cell_factor = 0.0;
     int64_t n_src_tot = 0, n_tgt_tot = 0, cs_tot = 0;
-    int key_bits = 0, tkey_bits = 0, max_stride = 1;
+    int key_bits = 0, tkey_bits = 0;
     void *ws = nullptr;
     BatchProb *probs_d = nullptr;
     GridParams *params = nullptr;
@@ -249,6 +249,7 @@ struct BatchPlan {
     int n_items = 0;
     // per class of problems: its slice [cls_begin, cls_end) of the queue
     std::vector<int> cls_begin, cls_end;
+    std::vector<int> cls_stride;      // most LDS words of a target, per class
     int32_t *summary = nullptr;       // device [4]
 
     std::vector<int> outer;           // problems of dimension > 3: one-problem kernel
