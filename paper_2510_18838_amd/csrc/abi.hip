@@ -344,6 +344,7 @@ void operator_mem_free(Operator &op)
 
 namespace {
 size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
+constexpr int64_t kDirectTargets = 49152;
 // workspace of a transfer on a grid:
 // [summary | tperm | svals | staged outputs | sort buffers]
 struct TransferWs {
@@ -487,7 +488,10 @@ pcms_status transfer_on_grid(const Grid *g, const double *src_vals, int32_t n_fi
     int32_t *summary = async ? o.summary : (int32_t *)ws;
     int *tperm = (int *)((char *)ws + L.off_tperm);
     double *svals = (double *)((char *)ws + L.off_svals);
-    double *stage = (double *)((char *)ws + L.off_stage);
+    // few targets write their fields directly: their scattered stores cost
+    // less than the launch that transposes staged records (6 us)
+    const bool direct = n_tgt <= kDirectTargets;
+    double *stage = direct ? nullptr : (double *)((char *)ws + L.off_stage);
     if ((st = zero_ints(summary, 4, s)) != PCMS_OK) return st;
     if ((st = g_prof.mark(1)) != PCMS_OK) return st;
     // the target order: forked off already, forked off now (to overlap the
@@ -509,7 +513,7 @@ pcms_status transfer_on_grid(const Grid *g, const double *src_vals, int32_t n_fi
                          stage, status, s);
     if (st != PCMS_OK) return st;
     if ((st = g_prof.mark(4)) != PCMS_OK) return st;
-    if ((st = unstage_fields(stage, n_tgt, n_fields, tgt_vals, s)) != PCMS_OK) return st;
+    if (!direct && (st = unstage_fields(stage, n_tgt, n_fields, tgt_vals, s)) != PCMS_OK) return st;
     if ((st = g_prof.mark(5)) != PCMS_OK) return st;
     if ((st = profile_end()) != PCMS_OK) return st;
     return finish(summary, async, s, true);

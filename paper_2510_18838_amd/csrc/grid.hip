@@ -24,35 +24,14 @@ constexpr int kSortItems = kSortThreads * kSortRounds;
 constexpr int kScanThreads = 256;
 constexpr int kScanItems = 4 * kScanThreads;
 
-__device__ inline long long ordered_key(double x)
-{
-    long long b = __double_as_longlong(x);
-    return b >= 0 ? b : (b ^ 0x7fffffffffffffffLL);
-}
-
-__device__ inline double ordered_val(long long k)
-{
-    long long b = k >= 0 ? k : (k ^ 0x7fffffffffffffffLL);
-    return __longlong_as_double(b);
-}
-
-__global__ void k_bbox_init(long long *bb, int dim)
-{
-    int k = threadIdx.x;
-    if (k < dim) {
-        bb[k] = 0x7fffffffffffffffLL;              // running min
-        bb[dim + k] = (long long)0x8000000000000000ULL;  // running max
-    }
-}
-
-// Per-dimension min/max of the points: wave reductions, then one atomic per
-// block and dimension.  Each lane takes kBboxUnroll points per step with
-// their loads issued together (the grid is capped at 1024 blocks to bound
-// the atomics, so a lane has several points and one at a time left the loop
-// bound by load latency).
-constexpr int kBboxUnroll = 4;
+// Per-dimension min/max of each block's points (part[block][2][D]), reduced
+// further by k_grid_params.  Each lane takes kBboxUnroll points per step with
+// their loads issued together (the grid is capped at kBboxBlocks blocks to
+// bound the second reduction, so a lane has several points and one at a time
+// left the loop bound by load latency).
+constexpr int kBboxUnroll = 4, kBboxBlocks = 1024;
 template <int D>
-__global__ void __launch_bounds__(256) k_bbox(const double *__restrict__ pts, int64_t n, long long *bb)
+__global__ void __launch_bounds__(256) k_bbox(const double *__restrict__ pts, int64_t n, double *__restrict__ part)
 {
     __shared__ double smn[4][D], smx[4][D];
     double mn[D], mx[D];
@@ -103,25 +82,39 @@ __global__ void __launch_bounds__(256) k_bbox(const double *__restrict__ pts, in
             a = fmin(a, smn[v][k]);
             b = fmax(b, smx[v][k]);
         }
-        if (a <= b) {
-            atomicMin(&bb[k], ordered_key(a));
-            atomicMax(&bb[D + k], ordered_key(b));
-        }
+        part[(size_t)blockIdx.x * 2 * D + k] = a;
+        part[(size_t)blockIdx.x * 2 * D + D + k] = b;
     }
 }
 
-// Chooses the bucket widths (one thread).
-__global__ void k_grid_params(const long long *bb, int dim, int64_t n, const double *g,
-                              double cell_width, double pts_per_cell, int cap, int sub,
-                              GridParams *gp)
+struct Metric {
+    double g[kMaxDim];
+};
+
+// The bounding box from the n_part blocks' partial ones, and the bucket widths
+// (one thread).  The metric comes by value: a copy from host memory is a
+// launch of its own, and waits for the host.
+__global__ void __launch_bounds__(256)
+k_grid_params(const double *__restrict__ part, int n_part, int dim, int64_t n, Metric g,
+              double cell_width, double pts_per_cell, int cap, int sub, GridParams *gp)
 {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
+    __shared__ double s[2 * kMaxDim][4];
+    const int t = threadIdx.x;
+    for (int k = 0; k < 2 * dim; ++k) {
+        const double sign = k < dim ? 1.0 : -1.0;   // the maximum as a minimum
+        double m = INFINITY;
+        for (int b = t; b < n_part; b += 256) m = fmin(m, sign * part[(size_t)b * 2 * dim + k]);
+        for (int off = 32; off > 0; off >>= 1) m = fmin(m, __shfl_xor(m, off));
+        if ((t & 63) == 0) s[k][t >> 6] = m;
+    }
+    __syncthreads();
+    if (t != 0) return;
     double lo[kMaxDim], hi[kMaxDim];
     for (int k = 0; k < dim; ++k) {
-        lo[k] = ordered_val(bb[k]);
-        hi[k] = ordered_val(bb[dim + k]);
+        lo[k] = fmin(fmin(s[k][0], s[k][1]), fmin(s[k][2], s[k][3]));
+        hi[k] = -fmin(fmin(s[dim + k][0], s[dim + k][1]), fmin(s[dim + k][2], s[dim + k][3]));
     }
-    grid_params_compute(lo, hi, dim, n, g, cell_width, pts_per_cell, cap, sub, gp);
+    grid_params_compute(lo, hi, dim, n, g.g, cell_width, pts_per_cell, cap, sub, gp);
 }
 
 template <int D>
@@ -177,15 +170,17 @@ pcms_status bucket_keys(int dim, const GridParams *gp, const double *pts, int64_
     return PCMS_OK;
 }
 
-pcms_status bbox(int dim, const double *pts, int64_t n, long long *bb, hipStream_t s)
+int bbox_blocks(int64_t n) { return (int)std::min<int64_t>((n + 255) / 256, kBboxBlocks); }
+
+pcms_status bbox(int dim, const double *pts, int64_t n, double *part, hipStream_t s)
 {
-    const int blocks = (int)std::min<int64_t>((n + 255) / 256, 1024);
+    const int blocks = bbox_blocks(n);
     switch (dim) {
-    case 1: k_bbox<1><<<blocks, 256, 0, s>>>(pts, n, bb); break;
-    case 2: k_bbox<2><<<blocks, 256, 0, s>>>(pts, n, bb); break;
-    case 3: k_bbox<3><<<blocks, 256, 0, s>>>(pts, n, bb); break;
-    case 4: k_bbox<4><<<blocks, 256, 0, s>>>(pts, n, bb); break;
-    default: k_bbox<5><<<blocks, 256, 0, s>>>(pts, n, bb); break;
+    case 1: k_bbox<1><<<blocks, 256, 0, s>>>(pts, n, part); break;
+    case 2: k_bbox<2><<<blocks, 256, 0, s>>>(pts, n, part); break;
+    case 3: k_bbox<3><<<blocks, 256, 0, s>>>(pts, n, part); break;
+    case 4: k_bbox<4><<<blocks, 256, 0, s>>>(pts, n, part); break;
+    default: k_bbox<5><<<blocks, 256, 0, s>>>(pts, n, part); break;
     }
     PCMS_HIP(hipGetLastError());
     return PCMS_OK;
@@ -250,6 +245,94 @@ __device__ __forceinline__ int scan_digits(int c, int *s)
     return s[t] - c;
 }
 
+// Ranks of a wave's keys (slot first + 64 r, r < kSortRounds; valid below n)
+// among the earlier ones of their digit, the digits' counts left in cnt: the
+// wave's running count of the digit plus the earlier lanes of the round (wave
+// multisplit).
+__device__ __forceinline__ void wave_ranks(const unsigned (&key)[kSortRounds], int first, int n,
+                                           int shift, int *cnt, int (&pos)[kSortRounds])
+{
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int r = 0; r < kSortRounds; ++r) {
+        const bool valid = first + r * 64 < n;
+        const int digit = (key[r] >> shift) & 255;
+        unsigned long long bits[8];
+#pragma unroll
+        for (int b = 0; b < 8; ++b) bits[b] = __ballot((digit >> b) & 1);
+        const unsigned long long mask = digit_match(__ballot(valid), bits, digit);
+        const int rank = __popcll(mask & lanes_below(lane));
+        // one wave's LDS accesses are ordered: every lane reads the count
+        // before the digit's first lane raises it
+        pos[r] = cnt[digit] + rank;
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        if (valid && rank == 0) cnt[digit] += __popcll(mask);
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    }
+}
+
+// All passes over at most kSortItems keys, in one block.
+__global__ void __launch_bounds__(kSortThreads)
+k_sort_block(unsigned *__restrict__ keys, int *__restrict__ vals, int n, int shift, int passes)
+{
+    __shared__ int cnt[4][256];
+    __shared__ int lstart[256], scan[256];
+    __shared__ unsigned skey[kSortItems];
+    __shared__ int sval[kSortItems];
+    const int t = threadIdx.x, w = t >> 6;
+    const int first = w * (kSortItems / 4) + (t & 63);
+    unsigned key_r[kSortRounds];
+    int val_r[kSortRounds], pos_r[kSortRounds];
+#pragma unroll
+    for (int r = 0; r < kSortRounds; ++r) {
+        const int i = first + r * 64;
+        key_r[r] = i < n ? keys[i] : 0u;
+        val_r[r] = i < n ? vals[i] : 0;
+    }
+    for (int ps = 0; ps < passes; ++ps, shift += 8) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) cnt[v][t] = 0;
+        __syncthreads();
+        wave_ranks(key_r, first, n, shift, cnt[w], pos_r);
+        __syncthreads();
+        int run = 0;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int c = cnt[v][t];
+            cnt[v][t] = run;
+            run += c;
+        }
+        lstart[t] = scan_digits(run, scan);
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kSortRounds; ++r) {
+            if (first + r * 64 < n) {
+                const int digit = (key_r[r] >> shift) & 255;
+                const int p = lstart[digit] + cnt[w][digit] + pos_r[r];
+                skey[p] = key_r[r];
+                sval[p] = val_r[r];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kSortRounds; ++r) {
+            const int i = first + r * 64;
+            if (i < n) {
+                key_r[r] = skey[i];
+                val_r[r] = sval[i];
+            }
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < kSortRounds; ++r) {
+        const int i = first + r * 64;
+        if (i < n) {
+            keys[i] = key_r[r];
+            vals[i] = val_r[r];
+        }
+    }
+}
+
 // One block's kSortItems keys, each wave ranking its own quarter of them: the
 // rank of a key among its digit's in the quarter is the wave's running count
 // of the digit plus the earlier lanes of the round (wave multisplit), with no
@@ -273,9 +356,9 @@ k_digit_scatter(const unsigned *__restrict__ kin, const int *__restrict__ vin, i
     __shared__ int lstart[256], gstart[256], scan[256];
     __shared__ unsigned skey[kSortItems];
     __shared__ int sval[kSortItems];
-    const int t = threadIdx.x, w = t >> 6, lane = t & 63;
+    const int t = threadIdx.x, w = t >> 6;
     const int base = blockIdx.x * kSortItems;
-    const int first = base + w * (kSortItems / 4) + lane;
+    const int first = base + w * (kSortItems / 4) + (t & 63);
 #pragma unroll
     for (int v = 0; v < 4; ++v) cnt[v][t] = 0;
     unsigned key_r[kSortRounds];
@@ -287,22 +370,7 @@ k_digit_scatter(const unsigned *__restrict__ kin, const int *__restrict__ vin, i
         val_r[r] = i < n ? vin[i] : 0;
     }
     __syncthreads();
-#pragma unroll
-    for (int r = 0; r < kSortRounds; ++r) {
-        const bool valid = first + r * 64 < n;
-        const int digit = (key_r[r] >> shift) & 255;
-        unsigned long long bits[8];
-#pragma unroll
-        for (int b = 0; b < 8; ++b) bits[b] = __ballot((digit >> b) & 1);
-        const unsigned long long mask = digit_match(__ballot(valid), bits, digit);
-        const int rank = __popcll(mask & lanes_below(lane));
-        // one wave's LDS accesses are ordered: every lane reads the count
-        // before the digit's first lane raises it
-        pos_r[r] = cnt[w][digit] + rank;
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        if (valid && rank == 0) cnt[w][digit] += __popcll(mask);
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    }
+    wave_ranks(key_r, first, n, shift, cnt[w], pos_r);
     __syncthreads();
     // digit t: the waves' offsets in its run, the run's start in the block,
     // and its global offset less that start
@@ -423,14 +491,19 @@ int key_bits(int n_cells_cap)
 constexpr int kDirectBlocks = 32;
 
 // Sorts (keys, vals) stably by key bits [lo_bit, bits); the result ends up
-// in (k0, v0).  Per pass a histogram, a scan for more than kDirectBlocks
-// blocks, and a scatter.
+// in (k0, v0).  One launch for one block's keys; else per pass a histogram, a
+// scan for more than kDirectBlocks blocks, and a scatter.
 pcms_status radix_sort(unsigned *k0, int *v0, unsigned *k1, int *v1, int n, int bits, int *hist,
                        hipStream_t s, int lo_bit = 0)
 {
     int nb = (n + kSortItems - 1) / kSortItems;
     if (nb == 0) return PCMS_OK;
     int passes = std::max(1, (bits - lo_bit + 7) / 8);
+    if (nb == 1) {
+        k_sort_block<<<1, kSortThreads, 0, s>>>(k0, v0, n, lo_bit, passes);
+        PCMS_HIP(hipGetLastError());
+        return PCMS_OK;
+    }
     unsigned *kin = k0, *kout = k1;
     int *vin = v0, *vout = v1;
     for (int ps = 0; ps < passes; ++ps) {
@@ -593,22 +666,22 @@ int cells_cap_for(int64_t n_src)
 
 size_t grid_build_scratch_bytes(int64_t n_src)
 {
-    // bbox keys + metric copy + sort buffers
+    // sort buffers (and spare: the sizes are kept)
     return 256 + sort_scratch_bytes((int)n_src) + 64 * sizeof(double);
 }
 
-pcms_status source_bbox_params(Grid *grid, const double *src, double *gdev, long long *bb,
-                               double cell_width, double pts_per_cell, hipStream_t s)
+pcms_status source_bbox_params(Grid *grid, const double *src, void *scratch, double cell_width,
+                               double pts_per_cell, hipStream_t s)
 {
     const int dim = grid->dim;
     const int n = (int)grid->n_src;
-    PCMS_HIP(hipMemcpyAsync(gdev, grid->g, sizeof(double) * dim, hipMemcpyHostToDevice, s));
-    k_bbox_init<<<1, 64, 0, s>>>(bb, dim);
-    PCMS_HIP(hipGetLastError());
-    pcms_status st = bbox(dim, src, n, bb, s);
+    double *part = (double *)scratch;
+    pcms_status st = bbox(dim, src, n, part, s);
     if (st != PCMS_OK) return st;
-    k_grid_params<<<1, 1, 0, s>>>(bb, dim, n, gdev, cell_width, pts_per_cell, grid->n_cells_cap,
-                                  row_slices(), grid->params);
+    Metric g;
+    for (int k = 0; k < kMaxDim; ++k) g.g[k] = grid->g[k];
+    k_grid_params<<<1, 256, 0, s>>>(part, bbox_blocks(n), dim, n, g, cell_width, pts_per_cell,
+                                    grid->n_cells_cap, row_slices(), grid->params);
     PCMS_HIP(hipGetLastError());
     return PCMS_OK;
 }
@@ -640,10 +713,6 @@ pcms_status build_grid_device(Grid *grid, const double *src, double cell_width,
     pcms_status st = scratch_alloc(&raw, bytes, s);
     if (st != PCMS_OK) return st;
     char *cur = (char *)raw;
-    long long *bb = (long long *)cur;
-    cur += 128;
-    double *gdev = (double *)cur;
-    cur += 128;
     unsigned *k0 = (unsigned *)cur;
     cur += sizeof(unsigned) * (size_t)n;
     unsigned *k1 = (unsigned *)cur;
@@ -652,8 +721,9 @@ pcms_status build_grid_device(Grid *grid, const double *src, double cell_width,
     cur += sizeof(int) * (size_t)n;
     int *hist = (int *)cur;
 
-    if ((st = source_bbox_params(grid, src, gdev, bb, cell_width, pts_per_cell, s)) != PCMS_OK)
-        return st;
+    // (the partial boxes, 80 bytes for each 256 sources, lie where the sort's
+    // buffers, 16 bytes for each source and 1 KB, will be)
+    if ((st = source_bbox_params(grid, src, raw, cell_width, pts_per_cell, s)) != PCMS_OK) return st;
     if (after_params && (st = (*after_params)()) != PCMS_OK) return st;
     if ((st = bucket_keys(grid->dim, grid->params, src, n, k0, grid->perm, grid_blocks(n, 256), s)) != PCMS_OK)
         return st;

@@ -64,11 +64,11 @@ pcms_status build_grid_device(Grid *grid, const double *src, double cell_width,
 // Stream-ordered scratch that build_grid_device takes while it runs.
 size_t grid_build_scratch_bytes(int64_t n_src);
 // The two stages build_grid_device shares with the LBVH build: the bounding
-// box and the GridParams of the sources (gdev: a device copy of the metric,
-// bb: the box keys, both scratch), and the sorted coordinate records and
-// inverse permutation from grid->perm.
-pcms_status source_bbox_params(Grid *grid, const double *src, double *gdev, long long *bb,
-                               double cell_width, double pts_per_cell, hipStream_t s);
+// box and the GridParams of the sources (scratch: 16-byte aligned, 80 bytes
+// for each 256 sources begun, at most 80 KB), and the sorted coordinate records
+// and inverse permutation from grid->perm.
+pcms_status source_bbox_params(Grid *grid, const double *src, void *scratch, double cell_width,
+                               double pts_per_cell, hipStream_t s);
 pcms_status gather_records(Grid *grid, const double *src, hipStream_t s);
 // LBVH over the sources (lbvh.hip): `grid` allocated with n_cells_cap = 1
 // and bvh_node_bytes() of records; leaves of at most max_leaf sources.

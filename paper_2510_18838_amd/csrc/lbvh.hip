@@ -324,10 +324,6 @@ pcms_status build_lbvh_device(Grid *g, const double *src, int max_leaf, hipStrea
     pcms_status st = scratch_alloc(&raw, sort_bytes + sizeof(int) * bvh_link_ints(n) + 256, s);
     if (st != PCMS_OK) return st;
     char *cur = (char *)raw;
-    long long *bb = (long long *)cur;
-    cur += 128;
-    double *gdev = (double *)cur;
-    cur += 128;
     unsigned *k0 = (unsigned *)cur;
     cur += sizeof(unsigned) * (size_t)n;
     unsigned *k1 = (unsigned *)cur;
@@ -340,7 +336,7 @@ pcms_status build_lbvh_device(Grid *g, const double *src, int max_leaf, hipStrea
     const TreeScratch w((int *)cur, n);
     g->lbvh = 1;   // before after_params: work forked there orders targets by Morton code
 
-    if ((st = source_bbox_params(g, src, gdev, bb, 0.0, (double)n, s)) != PCMS_OK) return st;
+    if ((st = source_bbox_params(g, src, raw, 0.0, (double)n, s)) != PCMS_OK) return st;
     if (after_params && (st = (*after_params)()) != PCMS_OK) return st;
     if ((st = morton_keys(dim, g->params, src, n, k0, g->perm, s)) != PCMS_OK) return st;
     if ((st = sort_pairs(k0, g->perm, k1, v1, n, 32, hist, s)) != PCMS_OK) return st;
