@@ -962,7 +962,7 @@ pcms_status pcms_batch_plan_create(const pcms_problem *problems, int32_t n,
             if (cf == 0.0) cf = tcf;
         }
     }
-    if (block == 0) block = 256;
+    if (block == 0) block = 64;   // (512 problems: 22768 us with 256, 22739 with 128, 21854 with 64)
     std::unique_ptr<BatchPlan> p(new (std::nothrow) BatchPlan());
     if (!p) return PCMS_ERR_NOMEM;
     p->n = n;

@@ -299,15 +299,36 @@ PCMS_HD PCMS_INLINE int nbr_target(const KArgs &a, const GridParams &gp, int i, 
     int n_found, n;
     double r2;
     const int st = select_target<D, UNIT, G>(S, a, n_found, n, r2);
-    for (int e = g.q; e < n; e += G) S.at(e) = a.perm[S.at(e)];
+    constexpr int kAtOnce = 8;
+    for (int e0 = g.q; e0 < n; e0 += kAtOnce * G) {
+        int v[kAtOnce];
+#pragma unroll
+        for (int u = 0; u < kAtOnce; ++u) v[u] = e0 + u * G < n ? a.perm[S.at(e0 + u * G)] : 0;
+#pragma unroll
+        for (int u = 0; u < kAtOnce; ++u)
+            if (e0 + u * G < n) S.at(e0 + u * G) = v[u];
+    }
     g.sync();
-    // source indices are distinct: each entry's rank is its output slot
+    // Source indices are distinct: each entry's rank is its output slot.  One
+    // reading of the list ranks kAtOnce entries (430k lists of 40:
+    // 1198 -> 716 us with one lane per target; one entry at a time read the
+    // whole list from LDS for each).
     int32_t *row = a.nbr + (size_t)ti * a.k_cap;
-    for (int e = g.q; e < n; e += G) {
-        const int v = S.at(e);
-        int rank = 0;
-        for (int x = 0; x < n; ++x) rank += S.at(x) < v;
-        row[rank] = v;
+    for (int e0 = g.q; e0 < n; e0 += kAtOnce * G) {
+        int v[kAtOnce], rank[kAtOnce];
+#pragma unroll
+        for (int u = 0; u < kAtOnce; ++u) {
+            v[u] = e0 + u * G < n ? S.at(e0 + u * G) : 0;
+            rank[u] = 0;
+        }
+        for (int x = 0; x < n; ++x) {
+            const int y = S.at(x);
+#pragma unroll
+            for (int u = 0; u < kAtOnce; ++u) rank[u] += y < v[u];
+        }
+#pragma unroll
+        for (int u = 0; u < kAtOnce; ++u)
+            if (e0 + u * G < n) row[rank[u]] = v[u];
     }
     if (g.q == 0) {
         a.n_kept[ti] = n;

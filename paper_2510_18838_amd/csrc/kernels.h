@@ -1,7 +1,7 @@
-// The one-problem neighbour-list and field-transfer kernels (one lane per
-// target, targets in tiled Morton order so that the lanes of a wave search
-// overlapping stencils), instantiated per dimension in mls_d1.hip ..
-// mls_d5.hip so that the variants compile in parallel.  The per-target work
+// The one-problem neighbour-list and field-transfer kernels (one or four lanes
+// per target, targets in tiled Morton order so that the lanes of a wave search
+// overlapping stencils), instantiated per dimension in mls_d1.hip .. mls_d5.hip
+// and mls4_d1.hip .. mls4_d5.hip so that the variants compile in parallel.  The per-target work
 // (search, moment assembly, Cholesky, evaluation) is in fit.h / search.h.
 #pragma once
 
@@ -12,8 +12,8 @@
 
 namespace pcms {
 
-// Lanes per target (G consecutive lanes of a wave): one, or four for calls of
-// few targets (target_lanes in mls.hip).  The block's targets are consecutive
+// Lanes per target (G consecutive lanes of a wave): one, or four for few
+// targets and for long lists (target_lanes in mls.hip).  The block's targets are consecutive
 // in processing order and each owns `stride` LDS words.
 constexpr int kQuad = 4;
 
@@ -60,13 +60,12 @@ __global__ void __launch_bounds__(256) k_neighbors(KArgs a)
 // Waves per SIMD the register allocator targets (168 VGPRs for 3, 256 for
 // 2): three, except for MIXED_REFINE in 4-D and 5-D (240-1100 bytes of
 // spill per lane under 168 VGPRs) and the 4-D and 5-D quadratic bases in
-// any precision (1-2 KB), which get two.  Measured: the 5-D linear
-// MIXED_REFINE kernel went from 3-6 % slower than FP64 to level with it
-// (74.3 against 76.1 ms, means of three runs).  The low-dimensional
-// kernels need the third wave for latency even where they spill a little:
-// at two, the 3-D quadratic MIXED_REFINE kernel (52 bytes of spill) slows
-// from 7.0 to 9.2 ms and the 2-D quadratic one (132 bytes) from 0.43 to
-// 0.48 ms.
+// any precision (1-2 KB), which get two.  Measured with the row walks that
+// the row tables replaced: the 5-D linear MIXED_REFINE kernel went from 3-6 %
+// slower than FP64 to level with it (74.3 against 76.1 ms).  The
+// low-dimensional kernels need the third wave for latency even where they
+// spill a little: at two, the 3-D quadratic MIXED_REFINE kernel slowed from 7.0
+// to 9.2 ms and the 2-D quadratic one from 0.43 to 0.48 ms.
 template <int PREC, int D, int P>
 constexpr int waves_for()
 {

@@ -100,36 +100,60 @@ int lane_words(const LaunchSpec &ls)
 int target_stride(const LaunchSpec &ls) { return lane_words(ls) | 1; }
 
 // Lanes per target.  A lane alone takes its target's some hundred dependent
-// loads one after another, which only pays when there are enough targets to
-// fill the chip with waves; below that, four lanes share a target's candidates
-// and the loads of its fit.  Kernel times with one lane and with four (the
-// groups' collectives and repeated arithmetic make four lose once the waves
-// queue): 2-D linear, 1.5k targets, 76 and 37 us; 3-D linear, 15k targets, 118
-// and 62 us; 3-D linear, 30k targets among 3M sources, 376 and 215 us; 3-D
-// quadratic, 500k targets, 733 and 967 us.  The line is one wave of quads for
-// each of 3 x 1024 SIMD slots.
+// loads one after another, which only pays when enough waves are resident to
+// hide them; four lanes share a target's candidates and the loads of its fit,
+// and its LDS is a quarter per wave, but they repeat the fit's arithmetic.
+// Four pay where
+// * there are few targets: kernel times with one lane and with four: 2-D linear,
+//   1.5k targets, 76 and 37 us; 3-D linear, 15k targets, 118 and 62 us; 3-D
+//   linear, 30k targets among 3M sources, 376 and 215 us; 3-D quadratic, 500k
+//   targets, 733 and 967 us.  The line is one wave of quads for each of
+//   3 x 1024 SIMD slots.
+// * or long lists leave few one-lane waves per CU, the fit is small, and the
+//   radius is not a k-th distance (whose window walks share badly).  Calls in
+//   us with one lane and with four, growing radius: 5-D linear FP64, 1M
+//   targets, k_cap 96 (5 waves): 16121 and 9600, MIXED_REFINE 16279 and 12763;
+//   5-D k_cap 80 (6 waves) 1023 and 884, MIXED_REFINE 1029 and 1083; k_cap 128
+//   (4 waves): 4-D 1377 and 1063, 3-D 1188 and 1065, 2-D 738 and 762; k_cap 96
+//   in 3-D (5 waves) 906 and 958; quadratic bases lose everywhere (4-D, k_cap
+//   96: 4605 and 11204).
+// * The lists alone have no fit, and the ranking by source index is shared:
+//   growing radius, k_cap 64 (7-8 waves): 2-D 497 and 397, 3-D 601 and 500,
+//   4-D 613 and 563, 5-D 938 and 817; k_cap 32 420 and 426 (3-D).  k-th
+//   distances: k 85 (6 waves) 1016 and 743 (2-D), 1347 and 1039 (3-D), 4151
+//   and 3664 (5-D); k 64 (8 waves) 1681 and 1673 (4-D), 2496 and 2564 (5-D).
 constexpr int64_t kQuadTargets = 49152;
-int target_lanes(const LaunchSpec &ls)
+constexpr int kListsAlone = -1;   // for a degree
+int target_lanes(const LaunchSpec &ls, int degree)
 {
-    return !ls.grid->lbvh && ls.n_tgt <= kQuadTargets ? kQuad : 1;
+    if (ls.grid->lbvh) return 1;
+    if (ls.n_tgt <= kQuadTargets) return kQuad;
+    const int waves = (160 << 10) / (64 * target_stride(ls) * (int)sizeof(int));
+    const bool knn = ls.radius.mode == PCMS_RADIUS_KNN;
+    if (degree == kListsAlone) return waves <= (knn ? 6 : 9) ? kQuad : 1;
+    const int dim = ls.grid->dim;
+    return degree <= 1 && !knn && dim >= 3 && waves <= (dim == 5 ? 5 : 4) ? kQuad : 1;
 }
 
-// Threads per block; the targets' LDS must fit 64 KiB per workgroup.  Quads
-// take one wave per block, to spread few targets over the CUs.
-int pick_block(int requested, const LaunchSpec &ls)
+// Threads per block; the targets' LDS must fit 64 KiB per workgroup.  Single
+// waves fill what the LDS of a CU leaves (5-D linear, k_cap 96, 2M targets, one
+// lane per target: blocks of 128, the most that fit, keep 4 waves and take 44.8
+// ms, single waves 5 and 31.2), and no wave waits for its block's others: 1M
+// neighbour lists 1243 -> 1154 us, the LBVH 4281 -> 4195; the 3-D quadratic
+// kernel measures the same (4.26 and 4.28 ms).
+int pick_block(int requested, const LaunchSpec &ls, int lanes)
 {
-    const int lanes = target_lanes(ls);
-    int b = requested > 0 ? requested : lanes > 1 ? 64 : 256;
+    int b = requested > 0 ? requested : 64;
     while (b > 64 && (size_t)(b / lanes) * target_stride(ls) * sizeof(int) > 65536) b >>= 1;
     return b;
 }
 
-size_t block_lds(int block, const LaunchSpec &ls)
+size_t block_lds(int block, const LaunchSpec &ls, int lanes)
 {
-    return (size_t)(block / target_lanes(ls)) * target_stride(ls) * sizeof(int);
+    return (size_t)(block / lanes) * target_stride(ls) * sizeof(int);
 }
 
-KArgs base_args(const LaunchSpec &ls, int block)
+KArgs base_args(const LaunchSpec &ls, int block, int lanes)
 {
     KArgs a{};
     a.gp = ls.grid->params;
@@ -148,7 +172,7 @@ KArgs base_args(const LaunchSpec &ls, int block)
     a.max_iter = ls.radius.max_iter;
     a.r = ls.radius.r;
     a.k_cap = ls.k_cap;
-    const int tpb = block / target_lanes(ls);
+    const int tpb = block / lanes;
     a.n_blocks = (int)((ls.n_tgt + tpb - 1) / tpb);
     a.words = lane_words(ls);
     a.stride = target_stride(ls);
@@ -169,16 +193,17 @@ pcms_status launch_neighbors(const LaunchSpec &ls, int32_t *nbr, int32_t *n_kept
                              int32_t *n_found, double *r2, uint8_t *status, hipStream_t s)
 {
     if (ls.n_tgt == 0) return PCMS_OK;
-    const int block = pick_block(ls.block, ls);
-    KArgs a = base_args(ls, block);
+    const int lanes = target_lanes(ls, kListsAlone);
+    const int block = pick_block(ls.block, ls, lanes);
+    KArgs a = base_args(ls, block, lanes);
     a.nbr = nbr;
     a.n_kept = n_kept;
     a.n_found = n_found;
     a.r2 = r2;
     a.status = status;
-    KernelFn fn = nbr_for(ls.grid->dim, unit_metric(ls.grid), ls.grid->lbvh != 0, target_lanes(ls) > 1);
+    KernelFn fn = nbr_for(ls.grid->dim, unit_metric(ls.grid), ls.grid->lbvh != 0, lanes > 1);
     const int launch = launch_blocks(a.n_blocks);
-    const size_t shm = block_lds(block, ls);
+    const size_t shm = block_lds(block, ls, lanes);
     hipLaunchKernelGGL(fn, dim3(launch), dim3(block), shm, s, a);
     PCMS_HIP(hipGetLastError());
     return PCMS_OK;
@@ -189,8 +214,9 @@ pcms_status launch_transfer(const LaunchSpec &ls, const double *svals, int n_fie
                             double *stage, uint8_t *status, hipStream_t s)
 {
     if (ls.n_tgt == 0) return PCMS_OK;
-    const int block = pick_block(ls.block, ls);
-    KArgs a = base_args(ls, block);
+    const int lanes = target_lanes(ls, degree);
+    const int block = pick_block(ls.block, ls, lanes);
+    KArgs a = base_args(ls, block, lanes);
     a.svals = svals;
     a.nf = n_fields;
     a.nfs = padded_dim(n_fields);
@@ -200,9 +226,9 @@ pcms_status launch_transfer(const LaunchSpec &ls, const double *svals, int n_fie
     a.stage = stage;
     a.status = status;
     KernelFn fn = xfer_for(ls.grid->dim, degree, precision, unit_metric(ls.grid),
-                           ls.grid->lbvh != 0, target_lanes(ls) > 1);
+                           ls.grid->lbvh != 0, lanes > 1);
     const int launch = launch_blocks(a.n_blocks);
-    const size_t shm = block_lds(block, ls);
+    const size_t shm = block_lds(block, ls, lanes);
     hipLaunchKernelGGL(fn, dim3(launch), dim3(block), shm, s, a);
     PCMS_HIP(hipGetLastError());
     return PCMS_OK;
@@ -213,8 +239,9 @@ pcms_status launch_operator(const LaunchSpec &ls, int degree, int weight, int pr
                             uint8_t *status, hipStream_t s)
 {
     if (ls.n_tgt == 0) return PCMS_OK;
-    const int block = pick_block(ls.block, ls);
-    KArgs a = base_args(ls, block);
+    const int lanes = target_lanes(ls, degree);
+    const int block = pick_block(ls.block, ls, lanes);
+    KArgs a = base_args(ls, block, lanes);
     a.weight = weight;
     a.lambda = lambda;
     a.op_w = op_w;
@@ -222,9 +249,9 @@ pcms_status launch_operator(const LaunchSpec &ls, int degree, int weight, int pr
     a.op_n = op_n;
     a.status = status;
     KernelFn fn = op_for(ls.grid->dim, degree, precision, unit_metric(ls.grid),
-                         ls.grid->lbvh != 0, target_lanes(ls) > 1);
+                         ls.grid->lbvh != 0, lanes > 1);
     const int launch = launch_blocks(a.n_blocks);
-    const size_t shm = block_lds(block, ls);
+    const size_t shm = block_lds(block, ls, lanes);
     hipLaunchKernelGGL(fn, dim3(launch), dim3(block), shm, s, a);
     PCMS_HIP(hipGetLastError());
     return PCMS_OK;
