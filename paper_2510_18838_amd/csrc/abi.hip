@@ -839,6 +839,12 @@ pcms_status pcms_operator_build(const double *src, int64_t n_src, int32_t dim, c
     const size_t o_c = o_n + ((sizeof(int32_t) * nt + 255) & ~(size_t)255);
     const size_t o_w = o_c + ((sizeof(int32_t) * nt * op->width + 255) & ~(size_t)255);
     const size_t bytes = o_w + sizeof(double) * nt * op->width;
+    // (in a capture the pool would hand out memory that only the graph's
+    // replays own)
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+    PCMS_HIP(hipStreamIsCapturing(s, &capturing));
+    if (capturing != hipStreamCaptureStatusNone)
+        return hip_fail(hipErrorStreamCaptureUnsupported, "pcms_operator_build");
     hipMemPool_t pool;
     op->device = g.device;
     if ((st = operator_pool(op->device, &pool)) != PCMS_OK) return st;
