@@ -76,12 +76,18 @@ PCMS_HD PCMS_INLINE double ball_beyond(double x)
 //
 // All distances are in bucket widths (every dimension above 0 with more than
 // one bucket has the metric width gp.wm, dimension 0 the width wm / sub) and
-// relative to t's own bucket, so FP32 holds them to 1e-7 of a width however
-// many buckets there are.  The c_1 of a line (fixed c_2..c_{d-1}) are those of
-// the chord in that line, so no row out of reach is visited.  Every rounding
-// is covered by slack that can only widen a range (4e-6 relative on rho^2,
-// 2e-5 of a width; the bucket assignment rounds by far less).
+// relative to t's own bucket, so for t within the grid FP32 holds its offset
+// to 1e-7 of a width however many buckets there are.  The c_1 of a line (fixed
+// c_2..c_{d-1}) are those of the chord in that line, so no row out of reach is
+// visited.  Every rounding is covered by slack that can only widen a range:
+// 2e-5 of a width, 4e-6 relative on rho^2 and 2e-6 on a chord (the bucket
+// assignment rounds by far less).  The relative slack also covers t beyond the
+// grid, whose offset FP32 holds to 6e-8 of itself, as a ball that reaches the
+// grid is no smaller than the offset.  Offsets are clamped at kFar widths: a
+// radius up to kFar cannot reach beyond them, and a larger one takes every
+// row, as its rho^2 then exceeds the sum of the clamped offsets' squares.
 constexpr int kRows = 4;
+constexpr double kFar = 1e15;
 
 template <int D, bool DOWN>
 struct RowLines {
@@ -100,13 +106,14 @@ struct RowLines {
         : gp(gp_), cs(cs_), outer(0.0f), row(0), more(true)
     {
         const double iw = 1.0 / gp.wm;
-        rho2 = (float)fmin(r2 * iw * iw * (1.0 + 4e-6), 1e30);
+        const double x2 = r2 * iw * iw * (1.0 + 4e-6);
+        rho2 = x2 <= kFar * kFar ? (float)x2 : 1e37f;
 #pragma unroll
         for (int k = 0; k < D; ++k) {
             const double u = (t[k] - gp.lo[k]) * gp.inv_w[k];
             ct[k] = (int)fmin(fmax(floor(u), 0.0), (double)(gp.n[k] - 1));
             // (a single bucket reaches everywhere; a flat dimension's width is not wm)
-            fr[k] = gp.n[k] > 1 ? (float)fmin(fmax(u - (double)ct[k], -1e15), 1e15) : 0.5f;
+            fr[k] = gp.n[k] > 1 ? (float)fmin(fmax(u - (double)ct[k], -kFar), kFar) : 0.5f;
             if (k >= 1) row += ct[k] * gp.stride[k];
         }
         if constexpr (D >= 3) {
