@@ -269,8 +269,10 @@ pcms_status pcms_operator_export(const pcms_operator *op, int32_t stride, pcms_s
 /* Slots per target of the operator (0 for NULL). */
 int32_t pcms_operator_width(const pcms_operator *op);
 
-/* Release the operator (waits for the device first).  Up to 1 GiB per device
- * of released operators' memory is kept for the next pcms_operator_build. */
+/* Release the operator (waits for its device first, whichever is current).
+ * If that fails (PCMS_ERR_HIP), the operator is still there and can be released
+ * again.  Up to 1 GiB per device of released operators' memory is kept for the
+ * next pcms_operator_build. */
 pcms_status pcms_operator_free(pcms_operator *op);
 
 /* ---------------------------------------------------------------------- */

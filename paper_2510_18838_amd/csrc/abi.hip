@@ -326,19 +326,27 @@ pcms_status operator_pool(int dev, hipMemPool_t *out)
 }
 
 // Gives an operator's block back to its device's pool, and what the pool holds
-// beyond kOperatorKeep to the device.  The device is idle.
-void operator_mem_free(Operator &op)
+// beyond kOperatorKeep to the device.  Work on any stream of the device may
+// still read the block, and giving it back waits for none of it, so the
+// operator's device (not the current one) is waited for first.  On an error the
+// block stays the operator's.
+pcms_status operator_mem_free(Operator &op)
 {
-    if (!op.mem) return;
+    if (!op.mem) return PCMS_OK;
     int dev = op.device;
     (void)hipGetDevice(&dev);
-    if (dev != op.device) (void)hipSetDevice(op.device);
-    (void)hipFreeAsync(op.mem, nullptr);
-    (void)hipStreamSynchronize(nullptr);
-    hipMemPool_t pool;
-    if (operator_pool(op.device, &pool) == PCMS_OK) (void)hipMemPoolTrimTo(pool, kOperatorKeep);
+    if (dev != op.device) PCMS_HIP(hipSetDevice(op.device));
+    hipError_t e = hipDeviceSynchronize();
+    if (e == hipSuccess) e = hipFreeAsync(op.mem, nullptr);
+    if (e == hipSuccess) {
+        op.mem = nullptr;
+        (void)hipStreamSynchronize(nullptr);
+        hipMemPool_t pool;
+        if (operator_pool(op.device, &pool) == PCMS_OK)
+            (void)hipMemPoolTrimTo(pool, kOperatorKeep);
+    }
     if (dev != op.device) (void)hipSetDevice(dev);
-    op.mem = nullptr;
+    return e == hipSuccess ? PCMS_OK : hip_fail(e, "release of the operator's memory");
 }
 }  // namespace
 
@@ -860,8 +868,10 @@ pcms_status pcms_operator_build(const double *src, int64_t n_src, int32_t dim, c
     op->op_c = (int32_t *)((char *)op->mem + o_c);
     op->op_w = (double *)((char *)op->mem + o_w);
     auto fail = [&](pcms_status e) {
+        const std::string msg = pcms_last_error();
         (void)hipStreamSynchronize(s);
-        operator_mem_free(*op);
+        (void)operator_mem_free(*op);
+        set_error(msg);   // the first failure's
         return e;
     };
     Scratch sc;
@@ -925,10 +935,9 @@ pcms_status pcms_operator_free(pcms_operator *op)
 {
     if (!op) return PCMS_OK;
     Operator *o = reinterpret_cast<Operator *>(op);
-    (void)hipDeviceSynchronize();
-    operator_mem_free(*o);
-    delete o;
-    return PCMS_OK;
+    const pcms_status st = operator_mem_free(*o);
+    if (st == PCMS_OK) delete o;
+    return st;
 }
 
 void pcms_batch_opts_default(pcms_batch_opts *o)

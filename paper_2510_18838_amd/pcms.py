@@ -576,7 +576,7 @@ class Operator:
 
     def free(self):
         if getattr(self, "handle", None):
-            lib().pcms_operator_free(self.handle)
+            _check(lib().pcms_operator_free(self.handle))
             self.handle = None
 
     def __del__(self):
