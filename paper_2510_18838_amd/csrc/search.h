@@ -404,7 +404,7 @@ struct Search {
     int words;  // >= max(k_cap, 2)
     Grp<G> g;
     BvhView bv; // the tree (BVH only)
-    int tab = 0;   // first word of the row table (scan32)
+    int lim = 0;   // words below it are the caller's during scan32
 
     PCMS_HD PCMS_INLINE int &at(int e)
     {
@@ -467,8 +467,11 @@ struct Search {
     // step pay for some lane's row.  A step's records are loaded before the
     // previous step's are used.  The earliest range stands first and is taken
     // first, so the words next to the caller's are free again first: f may use
-    // words below `tab` as it goes, and a table's candidates come in ascending
-    // order.  A table that does not hold all ranges is filled again.
+    // words below `lim` as it goes, up to the next range's word, which has been
+    // read.  That depends on the range alone and not on the step, so a list
+    // meets the table at the same candidate with any number of lanes.  A table's
+    // candidates come in ascending order; a table that does not hold all ranges
+    // is filled again.
     // False if it can hold none (no room, or a range too long).
     template <class U, class F>
     PCMS_HD PCMS_INLINE bool scan32(const Image32<D, UNIT> &im, double rho2, U &&used, F &&f)
@@ -509,7 +512,7 @@ struct Search {
             if (left && n == 0) fits = false;
             if (!g.all(fits)) return false;
             g.sync();
-            tab = words - n;
+            int tab = words - n;
             if (!R::kDown) {   // the earliest range first
                 for (int i = g.q; 2 * i < n - 1; i += G) {
                     const int x = at(tab + i), y = at(words - 1 - i);
@@ -528,13 +531,18 @@ struct Search {
             };
             if (n > 0) {
                 take();
+                int next_lim = min(tab + 1, words);
                 float s[kBatch32][D];
                 im.template load<G, kBatch32>(p, e, g.q, s);
                 for (;;) {
                     const int p0 = p, e0 = e;
+                    lim = next_lim;
                     p += kBatch32 * G;
                     const bool on = p < e || tab < words;
-                    if (p >= e && on) take();
+                    if (p >= e && on) {
+                        take();
+                        next_lim = min(tab + 1, words);
+                    }
                     float nx[kBatch32][D];
                     if (on) im.template load<G, kBatch32>(p, e, g.q, nx);
 #pragma unroll
@@ -612,7 +620,7 @@ struct Search {
                 const unsigned m = g.ballot(acc);
                 if (acc) {
                     const int pos = n + g.below(m);
-                    if (pos < tab) at(pos) = p;
+                    if (pos < lim) at(pos) = p;
                     else kept &= pos >= k_cap;
                 }
                 n += __builtin_popcount(m);
@@ -868,7 +876,7 @@ struct Search {
                 const unsigned ma = g.ballot(acc), ms = g.ballot(sure);
                 if (acc) {
                     const int pos = sure ? kReg + n + g.below(ms) : nm + g.below(ma & ~ms);
-                    if (pos < (sure ? tab : kReg)) at(pos) = p;
+                    if (pos < (sure ? lim : kReg)) at(pos) = p;
                     else room &= !sure;
                 }
                 n += __builtin_popcount(ms);
