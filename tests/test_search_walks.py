@@ -1,0 +1,34 @@
+"""The walks that a search takes (CPU emulation): a radius within the estimate's
+window costs two, and a wave waits for its longest target."""
+import re
+
+import pytest
+
+import emu_driver
+from paper_2510_18838_amd import synth
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _built():
+    emu_driver.build()
+
+
+def walks(p, lbvh=False, op=0):
+    """(mean over the targets, mean over the waves of their longest target's)"""
+    emu_driver.run(p, op, lbvh=lbvh)
+    err = emu_driver.run.last_stderr
+    return (float(re.search(r"target mean ([\d.]+)", err).group(1)),
+            float(re.search(r"wave max walks ([\d.]+)", err).group(1)))
+
+
+@pytest.mark.parametrize("lbvh", [False, True], ids=["grid", "tree"])
+@pytest.mark.parametrize("dim,k,k_cap", [(2, 20, 32), (3, 24, 32), (4, 30, 48), (5, 40, 64)])
+def test_nearest_in_the_windows_first_bin(dim, k, k_cap, lbvh):
+    """A k-th distance in the first of the window's 64 bins lies in the window.
+    Were it taken for one below, its target would take the general path (five
+    walks or more).  Two walks where the estimate holds and four where the k-th
+    is beside the window (4 % of these targets at most) keep the waves' mean of
+    their longest target below three."""
+    p = synth.uniform_problem(5, 20000, 2000, dim, 1, synth.KNN, n_fields=1, k=k, k_cap=k_cap)
+    mean, longest = walks(p, lbvh)
+    assert mean <= 2.08 and longest < 3.0, (mean, longest)
