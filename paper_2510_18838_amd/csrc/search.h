@@ -596,9 +596,10 @@ struct Search {
     }
 
     // Collects every source with D < r2 into the list (up to k_cap, in walk
-    // order); returns the count (the same on every lane of the group).  The
-    // walk reads FP32 records; a candidate between the two thresholds is
-    // decided from its FP64 record.
+    // order); returns the count (the same on every lane of the group), and
+    // leaves the list unfinished where it is above k_cap, as the k_cap nearest
+    // are then selected afresh.  The walk reads FP32 records; a candidate
+    // between the two thresholds is decided from its FP64 record.
     PCMS_HD PCMS_INLINE int collect(double r2)
     {
         const Image32<D, UNIT> im(gp, spts32, t, sqrt(r2));
@@ -607,8 +608,9 @@ struct Search {
         // In 1-D and 2-D, with few and long rows and FP64 records of one word,
         // the plain walk is as fast (2-D lattice, 1M targets: 345 us against
         // 355 with the FP32 records and 375 with the table).
-        bool kept = (D >= 3 || BVH) && out < INFINITY;
-        if (kept) {
+        bool done = false;
+        if ((D >= 3 || BVH) && out < INFINITY) {
+            bool kept = true;
             auto add = [&](int p, float d, bool ok) {
                 bool acc = ok & (d < out);
                 if (acc && !(d < in)) {
@@ -625,10 +627,10 @@ struct Search {
                 }
                 n += __builtin_popcount(m);
             };
-            kept &= scan32(im, r2, [&]() { return min(n, k_cap); }, add);
-            kept = g.all(kept);
+            done = scan32(im, r2, [&]() { return min(n, k_cap); }, add);
+            if (done && n <= k_cap) done = g.all(kept);
         }
-        if (!kept) {   // (or no FP32 threshold, or no room for the table)
+        if (!done) {   // (no FP32 threshold, no room for the table, or none for the list)
             n = 0;
             each_of<4>(Exact64<D, UNIT>{gp, spts, t}, r2, [&](int p, double d2, bool ok) {
                 const bool acc = ok & (d2 < r2);
@@ -854,11 +856,14 @@ struct Search {
         });
         g.sync();
         // (a count beyond 16 bits misleads, and is caught below)
-        int b = -1, cum = 0;
+        int b = -1, cum = 0, c_in = 0;   // c_in: images up to the end of bin b
         for (int j = 0; j < nbw; ++j) {
             const unsigned x = (unsigned)at(j);
             const int c0 = cum + (int)(x & 0xffffu), c1 = c0 + (int)(x >> 16);
-            if (b < 0 && c1 >= k) b = c0 >= k ? 2 * j : 2 * j + 1;
+            if (b < 0 && c1 >= k) {
+                b = c0 >= k ? 2 * j : 2 * j + 1;
+                c_in = c0 >= k ? c0 : c1;
+            }
             cum = c1;
         }
         g.sync();   // every lane has read the bins before the list overwrites them
@@ -868,6 +873,10 @@ struct Search {
             if (side) *side = b < 0 ? 1 : -1;
             return false;
         }
+        // All of these would be listed or set aside, so a window whose k-th
+        // bin is too full is given up after one walk (a radius that grew far
+        // beyond the cap).
+        if (c_in > words) return false;
         const double m = im.bound(hi) + 1e-6 * hi;
         const double e0 = lo + (double)(b - 1) * bw - m, e1 = lo + (double)b * bw + m;
         const float in = im.inside(e0), out = im.outside(e1);
@@ -876,7 +885,7 @@ struct Search {
         int n = 0, nm = 0;
         bool room = words >= kReg + k;
         if (room) {
-            room &= scan32(im, e1, [&]() { return kReg + min(n, k); }, [&](int p, float d, bool ok) {
+            const bool whole = scan32(im, e1, [&]() { return kReg + min(n, k); }, [&](int p, float d, bool ok) {
                 const bool acc = ok & (d < out), sure = acc & (d < in);
                 const unsigned ma = g.ballot(acc), ms = g.ballot(sure);
                 if (acc) {
@@ -888,7 +897,8 @@ struct Search {
                 nm += __builtin_popcount(ma & ~ms);
             });
             g.sync();
-            room = g.all(room);
+            if (whole && n + nm > words) return false;
+            room = g.all(room && whole);
             // (fewer than k, or k below e0: only where the images mislead)
             if (room && (n >= k || n + nm < k)) return false;
         }
@@ -1173,7 +1183,9 @@ struct Search {
         }
         // (one call site, so that the selection is inlined once)
         for (int attempt = 0; attempt < (D >= 4 ? 2 : 1); ++attempt) {
-            if (select_window<true>(k_cap, lo, hi, vw, nw)) return nw;
+            int side = 0;
+            if (select_window<true>(k_cap, lo, hi, vw, nw, &side)) return nw;
+            if (side == 0) break;   // in the window, but too many: wider bins hold more
             lo = 0.0;
             hi = r2;
         }

@@ -32,3 +32,19 @@ def test_nearest_in_the_windows_first_bin(dim, k, k_cap, lbvh):
     p = synth.uniform_problem(5, 20000, 2000, dim, 1, synth.KNN, n_fields=1, k=k, k_cap=k_cap)
     mean, longest = walks(p, lbvh)
     assert mean <= 2.08 and longest < 3.0, (mean, longest)
+
+
+@pytest.mark.parametrize("dim,mode,lbvh,bar", [
+    (2, synth.FIXED, True, 5.2), (3, synth.FIXED, False, 5.0), (4, synth.FIXED, False, 4.5),
+    (5, synth.FIXED, False, 4.5), (2, synth.GROW, True, 3.1), (3, synth.GROW, True, 3.1)])
+def test_capped_targets(dim, mode, lbvh, bar):
+    """About 70 sources in the ball and a cap of 32.  One walk counts them: the
+    list, which is selected afresh, costs no second one where it met the row
+    table.  With a growing radius two more select the cap's nearest.  With a
+    fixed one, whose words are the cap's alone, the selection gives up after its
+    first walk and the general path takes two to four."""
+    n = 8000
+    r = (70 / (n * synth.unit_ball_volume(dim))) ** (1.0 / dim)
+    p = synth.uniform_problem(5, n, 400, dim, 1, mode, n_fields=1, radius=r, n_min=8, k_cap=32)
+    mean, _ = walks(p, lbvh)
+    assert mean <= bar, mean
