@@ -270,17 +270,12 @@ struct BvhIter {
         : nodes(bv.nodes), within(gp, t, rho2), r(0)
     {
     }
-    // Visits one record: a leaf's range if it is one within reach, else an
-    // empty one; false after the last.
-    PCMS_HD PCMS_INLINE bool next(int &beg, int &end)
+    static constexpr int S = bvh_stride(D);
+    PCMS_HD PCMS_INLINE void load(float (&rec)[S])
     {
-        constexpr int S = bvh_stride(D);
-        beg = end = 0;
-        if (r < 0) return false;
 #ifdef PCMS_HOST_EMULATION
         ++pcms_emu_nodes;
 #endif
-        float rec[S];
         const float4 *q = reinterpret_cast<const float4 *>(nodes + (size_t)r * S);
 #pragma unroll
         for (int j = 0; j < S / 4; ++j) {
@@ -290,6 +285,15 @@ struct BvhIter {
             rec[4 * j + 2] = v.z;
             rec[4 * j + 3] = v.w;
         }
+    }
+    // Visits one record: a leaf's range if it is one within reach, else an
+    // empty one; false after the last.
+    PCMS_HD PCMS_INLINE bool next(int &beg, int &end)
+    {
+        beg = end = 0;
+        if (r < 0) return false;
+        float rec[S];
+        load(rec);
         const bool hit = within(rec);
         const int c0 = bvh_int(rec, 2 * D), rope = bvh_int(rec, 2 * D + 1);
         r = c0 < 0 || !hit ? rope : c0;
@@ -298,6 +302,23 @@ struct BvhIter {
             end = bvh_int(rec, 2 * D + 3);
         }
         return true;
+    }
+    // Calls leaf(beg, end) for every range.
+    template <class L>
+    PCMS_HD PCMS_INLINE void each(L &&leaf)
+    {
+        while (r >= 0) {
+            float rec[S];
+            load(rec);
+            const bool hit = within(rec);
+            const int c0 = bvh_int(rec, 2 * D), rope = bvh_int(rec, 2 * D + 1);
+            if (c0 < 0) {
+                if (hit) leaf(bvh_int(rec, 2 * D + 2), bvh_int(rec, 2 * D + 3));
+                r = rope;
+            } else {
+                r = hit ? c0 : rope;
+            }
+        }
     }
 };
 

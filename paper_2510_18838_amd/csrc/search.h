@@ -32,8 +32,13 @@ namespace pcms {
 
 // Candidates per walk step whose loads are issued together: FP64 records
 // (two 16-byte loads each in 3-D) and FP32 records (a lane's are adjacent and
-// load as whole 16-byte words: three words for four 3-D sources).
-constexpr int kBatch64 = 2, kBatch32 = 4;
+// load as whole 16-byte words: three words for four 3-D sources).  The
+// FP64 walks are the general path's, which targets in strongly non-uniform
+// clouds take.  With two and four records, 300k graded sources, 200k targets:
+// kNN 3-D linear 11636 and 9556 us, growing radius 2-D 8986 and 7512, 3-D 12840
+// and 10927; on the tree, 600k sources with far outliers, 3-D linear 108159 and
+// 104272, quadratic MIXED_REFINE 100651 and 91445.
+constexpr int kBatch64 = 4, kBatch32 = 4;
 
 // Bins of the windowed selection.
 constexpr int kMaxBins = 64;
@@ -433,19 +438,26 @@ struct Search {
         using R = Ranges<D, UNIT, BVH, false>;
         count_walk();
         R rng(gp, cs, bv, t, rho2);
-        int beg[R::kSlots], end[R::kSlots];
-        while (rng.next(beg, end)) {
+        auto range = [&](int p, int e) {
+            count_range(p, e);
+            for (; p < e; p += kBatch * G) walk_step<D, G, kBatch>(meas, p, e, g.q, f);
+        };
+        if constexpr (BVH) {
+            rng.it.each(range);
+        } else {
+            int beg[R::kSlots], end[R::kSlots];
+            while (rng.next(beg, end)) {
 #pragma unroll 1
-            for (int u = 0; u < R::kSlots; ++u) {
-                int p = beg[0], e = end[0];
+                for (int u = 0; u < R::kSlots; ++u) {
+                    int p = beg[0], e = end[0];
 #pragma unroll
-                for (int x = 1; x < R::kSlots; ++x)
-                    if (u == x) {
-                        p = beg[x];
-                        e = end[x];
-                    }
-                count_range(p, e);
-                for (; p < e; p += kBatch * G) walk_step<D, G, kBatch>(meas, p, e, g.q, f);
+                    for (int x = 1; x < R::kSlots; ++x)
+                        if (u == x) {
+                            p = beg[x];
+                            e = end[x];
+                        }
+                    range(p, e);
+                }
             }
         }
     }
@@ -632,7 +644,7 @@ struct Search {
         }
         if (!done) {   // (no FP32 threshold, no room for the table, or none for the list)
             n = 0;
-            each_of<4>(Exact64<D, UNIT>{gp, spts, t}, r2, [&](int p, double d2, bool ok) {
+            each_of<kBatch64>(Exact64<D, UNIT>{gp, spts, t}, r2, [&](int p, double d2, bool ok) {
                 const bool acc = ok & (d2 < r2);
                 const unsigned m = g.ballot(acc);
                 if (acc) {
