@@ -25,6 +25,8 @@
 // predicate.
 #pragma once
 
+#include <type_traits>
+
 #include "bvh.h"
 #include "device_common.h"
 
@@ -248,6 +250,10 @@ struct Exact64 {
         }
     }
     PCMS_HD PCMS_INLINE double d2(const double (&s)[D]) const { return metric_d2<D, UNIT>(t, s, gp); }
+    // (Image32's bound and thresholds: the measure is exact)
+    PCMS_HD PCMS_INLINE double bound(double) const { return 0.0; }
+    PCMS_HD PCMS_INLINE double inside(double x) const { return x; }
+    PCMS_HD PCMS_INLINE double outside(double x) const { return x; }
 };
 
 // Image32 loads a source's FP32 record s32_k = fl32(s_k - lo_k) and returns
@@ -467,8 +473,8 @@ struct Search {
         each_of<kBatch64>(Exact64<D, UNIT>{gp, spts, t}, rho2, f);
     }
 
-    // Calls f(p, D32, valid) for the candidates of the ball D < rho2.  The
-    // ranges are first listed in a table at the end of the target's words (the
+    // Calls f(p, x, valid) for the candidates of the ball D < rho2, x the
+    // measure's value (the FP32 image, in general).  The ranges are first listed in a table at the end of the target's words (the
     // first used() words are the caller's), one word each: length (12 bits)
     // and start relative to the table's first range (20 bits).  Then one loop
     // steps through the candidates of all of them: a lane that has finished a
@@ -485,8 +491,8 @@ struct Search {
     // candidates come in ascending order; a table that does not hold all ranges
     // is filled again.
     // False if it can hold none (no room, or a range too long).
-    template <class U, class F>
-    PCMS_HD PCMS_INLINE bool scan32(const Image32<D, UNIT> &im, double rho2, U &&used, F &&f)
+    template <class Meas, class U, class F>
+    PCMS_HD PCMS_INLINE bool scan32(const Meas &im, double rho2, U &&used, F &&f)
     {
         using R = Ranges<D, UNIT, BVH, true>;
         constexpr int S = R::kSlots;
@@ -544,7 +550,7 @@ struct Search {
             if (n > 0) {
                 take();
                 int next_lim = min(tab + 1, words);
-                float s[kBatch32][D];
+                typename Meas::E s[kBatch32][D];
                 im.template load<G, kBatch32>(p, e, g.q, s);
                 for (;;) {
                     const int p0 = p, e0 = e;
@@ -555,7 +561,7 @@ struct Search {
                         take();
                         next_lim = min(tab + 1, words);
                     }
-                    float nx[kBatch32][D];
+                    typename Meas::E nx[kBatch32][D];
                     if (on) im.template load<G, kBatch32>(p, e, g.q, nx);
 #pragma unroll
                     for (int j = 0; j < kBatch32; ++j) {
@@ -853,15 +859,24 @@ struct Search {
                                int *side = nullptr)
     {
         constexpr int kReg = 7;
-        const Image32<D, UNIT> im(gp, spts32, t, sqrt(hi));
+        // In 1-D the records are as large in FP64 as they are loaded, and a
+        // cloud of many sources has radii near the images' rounding, so that
+        // most of a window would be set aside (kNN 10, 1M targets among 4M and
+        // 20M uniform sources: 788 and 2567 us with the images).
+        using Meas = typename std::conditional<D == 1, Exact64<D, UNIT>, Image32<D, UNIT>>::type;
+        using E = typename Meas::E;
+        const Meas im = [&]() {
+            if constexpr (D == 1) return Meas{gp, spts, t};
+            else return Meas(gp, spts32, t, sqrt(hi));
+        }();
         const int nb = min(words, kMaxBins), nbw = (nb + 3) / 2;
         const double bw = (hi - lo) / nb;
-        const float hi32 = (float)hi, ibw = (float)(1.0 / bw), off = (float)(1.0 - lo / bw);
+        const E hi32 = (E)hi, ibw = (E)(1.0 / bw), off = (E)(1.0 - lo / bw);
         for (int j = g.q; j < nbw; j += G) at(j) = 0;
         g.sync();
-        const bool full = scan32(im, hi, [&]() { return nbw; }, [&](int, float d, bool ok) {
+        const bool full = scan32(im, hi, [&]() { return nbw; }, [&](int, E d, bool ok) {
             if (ok & (d < hi32)) {
-                const float y = fminf(fmaxf(__builtin_fmaf(d, ibw, off), 0.0f), (float)(nb + 1));
+                const float y = fminf(fmaxf((float)fma_t(d, ibw, off), 0.0f), (float)(nb + 1));
                 const int j = (int)y;
                 lds_add(&at(j >> 1), j & 1 ? 1 << 16 : 1);
             }
@@ -891,13 +906,13 @@ struct Search {
         if (c_in > words) return false;
         const double m = im.bound(hi) + 1e-6 * hi;
         const double e0 = lo + (double)(b - 1) * bw - m, e1 = lo + (double)b * bw + m;
-        const float in = im.inside(e0), out = im.outside(e1);
+        const E in = im.inside(e0), out = im.outside(e1);
         if (!(out < INFINITY)) return false;
         // the first kReg words hold those set aside, the list follows
         int n = 0, nm = 0;
         bool room = words >= kReg + k;
         if (room) {
-            const bool whole = scan32(im, e1, [&]() { return kReg + min(n, k); }, [&](int p, float d, bool ok) {
+            const bool whole = scan32(im, e1, [&]() { return kReg + min(n, k); }, [&](int p, E d, bool ok) {
                 const bool acc = ok & (d < out), sure = acc & (d < in);
                 const unsigned ma = g.ballot(acc), ms = g.ballot(sure);
                 if (acc) {
@@ -970,7 +985,7 @@ struct Search {
         // many set aside, or no words for the table: they are listed at the
         // end of the words, the last one first, and ranked there
         int c_b = 0, n_b = 0;
-        each_of<kBatch32>(im, e1, [&](int p, float d, bool ok) {
+        each_of<kBatch32>(im, e1, [&](int p, E d, bool ok) {
             const bool acc = ok & (d < out), sure = acc & (d < in);
             const unsigned ma = g.ballot(acc), ms = g.ballot(sure);
             if (acc) {

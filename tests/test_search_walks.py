@@ -2,9 +2,11 @@
 window costs two, and a wave waits for its longest target."""
 import re
 
+import numpy as np
 import pytest
 
 import emu_driver
+import parity_cases as C
 from paper_2510_18838_amd import synth
 
 
@@ -48,3 +50,16 @@ def test_capped_targets(dim, mode, lbvh, bar):
     p = synth.uniform_problem(5, n, 400, dim, 1, mode, n_fields=1, radius=r, n_min=8, k_cap=32)
     mean, _ = walks(p, lbvh)
     assert mean <= bar, mean
+
+
+def test_1d_selection_is_exact():
+    """In 1-D the selection reads FP64 records: far from the cloud's corner (a
+    stray source lies a million cloud widths away) FP32 images tell nothing
+    apart, and every capped target would take the general path of six walks
+    instead of three (a bin too full for the words costs a few of them more)."""
+    rng = np.random.default_rng(11)
+    src = np.concatenate([rng.uniform(0.0, 1e-3, (3000, 1)), [[-1000.0]]])
+    p = C.custom(src, rng.uniform(0.0, 1.0, (1, 3001)), rng.uniform(2e-4, 8e-4, (200, 1)), 1,
+                 synth.GROW, radius=1e-5, n_min=8, k_cap=24)
+    mean, _ = walks(p)
+    assert mean < 4.0, mean
