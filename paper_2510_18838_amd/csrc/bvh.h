@@ -239,7 +239,8 @@ struct BoxTest32 {
         const double l = rho2 * (1.0 + 1e-5);
         float lf = (float)l;
         if ((double)lf < l) lf = nextafterf(lf, INFINITY);
-        lim = lf + 1e-43f;
+        // (where FP32 does not bound distances, every box passes)
+        lim = gp.max32 > 0.0f ? lf + 1e-43f : INFINITY;
     }
     // rec: the record's box, lower then upper corner
     PCMS_HD PCMS_INLINE bool operator()(const float *rec) const
@@ -252,7 +253,7 @@ struct BoxTest32 {
             if (!UNIT) gap *= g[k];
             acc = fmaf(gap, gap, acc);
         }
-        return acc <= lim;
+        return !(acc > lim);
     }
 };
 

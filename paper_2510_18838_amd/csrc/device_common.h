@@ -85,6 +85,7 @@ struct GridParams {
     double iqs[kMaxDim];    // 1 / qs
     double wm;              // metric bucket width (of dimension 0: wm / sub)
     double density;         // sources per unit metric volume of the bounding box
+    float max32;            // |t_k - lo_k| below which FP32 distances are bounded (0: never)
 };
 
 PCMS_HD PCMS_INLINE int bucket_of(const GridParams &p, int k, double x)
@@ -191,6 +192,13 @@ PCMS_HD inline void grid_params_compute(const double *lo, const double *hi, int 
     p.n_cells = s;
     p.wm = wm;
     p.density = d_eff > 0 ? (double)n / vol : 0.0;
+    // FP32 differences of coordinates must not overflow, and a metric factor must
+    // be a normal FP32 number, below 1e20: the error of a subnormal coordinate,
+    // 2^-149, then stays below the absolute slack of the bounds (1e-36 of Image32
+    // in search.h, 1e-43 of BoxTest32 in bvh.h)
+    p.max32 = 1e38f;
+    for (int k = 0; k < dim; ++k)
+        if (!(p.hi[k] - p.lo[k] < 1e38 && p.g[k] > 1.2e-38 && p.g[k] < 1e20)) p.max32 = 0.0f;
     *out = p;
 }
 

@@ -269,8 +269,9 @@ struct Exact64 {
 // sum_k A_k |u_k| <= |A| sqrt(D) and sqrt(D) <= (D / c + c) / 2 for any c > 0,
 // and adding the d roundings of the FP32 sum, gives alpha and beta (times a
 // safety factor of 1.5).  c is chosen near the thresholds of the walk, where
-// the bound is tightest.  Coordinates beyond the FP32 range give non-finite
-// thresholds, which the callers treat as "unknown".
+// the bound is tightest.  Differences that can overflow and metric factors
+// outside the range of the bound (GridParams::max32) give non-finite thresholds,
+// which the callers treat as "unknown".
 template <int D, bool UNIT>
 struct Image32 {
     using E = float;
@@ -284,16 +285,18 @@ struct Image32 {
     {
         constexpr double kA = 1.2e-7, kB = 3.1e-7, kR = 6.0e-8, kSafe = 1.5;
         double a2 = 0.0;
+        bool known = true;
 #pragma unroll
         for (int k = 0; k < D; ++k) {
             th[k] = (float)(t[k] - gp.lo[k]);
             g[k] = UNIT ? 1.0f : (float)gp.g[k];
+            known &= fabsf(th[k]) < gp.max32;
             const double ak = (UNIT ? 1.0 : gp.g[k]) * fabs((double)th[k]) * kA;
             a2 += ak * ak;
         }
         const double A = sqrt(a2);
         c = fmin(fmax(c, 1e-150), 1e150);
-        alpha = kSafe * (A * A + (1.0 + kB) * A * c) + 1e-36;
+        alpha = known ? kSafe * (A * A + (1.0 + kB) * A * c) + 1e-36 : INFINITY;
         beta = kSafe * ((1.0 + kB) * A / c + 2.0 * kB + kB * kB + D * kR) * (1.0 + 1e-6);
     }
     // Candidates p + j * G + q (j < B); the values of those at or past end
