@@ -235,12 +235,15 @@ struct KArgs {
 // 5-D, whose lists outgrow the table's many rows, 24 keep the table of a capped
 // list from running out, and the five waves per CU of k_cap = 96).  A fixed
 // radius keeps k_cap words: its rare capped targets take the general path.
+// Lists within `spare` of kMaxKcap take 8, so that a target has at most
+// kMaxWords.
+constexpr int kMaxWords = kMaxKcap + 8;
 PCMS_HD inline int target_words(int mode, int k, int k_cap, int dim = 3)
 {
     const int spare = dim >= 4 ? 24 : 11;
-    if (mode == PCMS_RADIUS_KNN && k + 8 < k_cap) return k + spare;
     if (mode == PCMS_RADIUS_FIXED) return k_cap < 2 ? 2 : k_cap;
-    return k_cap + (k_cap > kMaxKcap - spare ? 8 : spare);
+    const int list = mode == PCMS_RADIUS_KNN && k + 8 < k_cap ? k : k_cap;
+    return list + (list > kMaxKcap - spare ? 8 : spare);
 }
 // Most entries of a kept list.
 PCMS_HD inline int target_kept(int mode, int k, int k_cap)

@@ -135,7 +135,9 @@ int target_lanes(const LaunchSpec &ls, int degree)
     return degree <= 1 && !knn && dim >= 3 && waves <= (dim == 5 ? 5 : 4) ? kQuad : 1;
 }
 
-// Threads per block; the targets' LDS must fit 64 KiB per workgroup.  Single
+// Threads per block: the targets' LDS fits 64 KiB, or the block is one wave,
+// whose 64 targets of kMaxWords take 67,840 bytes at most (a workgroup may have
+// 160 KiB).  Single
 // waves fill what the LDS of a CU leaves (5-D linear, k_cap 96, 2M targets, one
 // lane per target: blocks of 128, the most that fit, keep 4 waves and take 44.8
 // ms, single waves 5 and 31.2), and no wave waits for its block's others: 1M
