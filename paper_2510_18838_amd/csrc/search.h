@@ -95,6 +95,9 @@ PCMS_HD PCMS_INLINE double ball_beyond(double x)
 // row, as its rho^2 then exceeds the sum of the clamped offsets' squares.
 constexpr int kRows = 4;
 constexpr double kFar = 1e15;
+// Beyond the last bucket from any (a grid has at most 2^30, and the sum of two
+// still fits an int).
+constexpr float kFarBuckets = 1073741824.0f;
 
 template <int D, bool DOWN>
 struct RowLines {
@@ -141,8 +144,8 @@ struct RowLines {
     PCMS_HD PCMS_INLINE void chord(int k, float rem)
     {
         const float h = __builtin_fmaf(sqrt_approx(rem), 1.0f + 2e-6f, 4e-5f);
-        a[k] = max((int)fminf(fmaxf(floorf(fr[k] - h), -1e9f), 1e9f), -ct[k]);
-        b[k] = min((int)fminf(fmaxf(floorf(fr[k] + h), -1e9f), 1e9f), gp.n[k] - 1 - ct[k]);
+        a[k] = max((int)fminf(fmaxf(floorf(fr[k] - h), -kFarBuckets), kFarBuckets), -ct[k]);
+        b[k] = min((int)fminf(fmaxf(floorf(fr[k] + h), -kFarBuckets), kFarBuckets), gp.n[k] - 1 - ct[k]);
         // t beyond the grid: the ball may miss it, its nearest bucket is kept
         a[k] = min(a[k], gp.n[k] - 1 - ct[k]);
         b[k] = max(b[k], -ct[k]);
@@ -214,8 +217,8 @@ struct RowLines {
                 at += x * gp.stride[1];
             }
             const float h = __builtin_fmaf(sqrt_approx(rem), (1.0f + 2e-6f) * (float)gp.sub, 4e-5f);
-            const int x0 = ct[0] + (int)fminf(fmaxf(floorf(fr[0] - h), -1e9f), 1e9f);
-            const int x1 = ct[0] + (int)fminf(fmaxf(floorf(fr[0] + h), -1e9f), 1e9f);
+            const int x0 = ct[0] + (int)fminf(fmaxf(floorf(fr[0] - h), -kFarBuckets), kFarBuckets);
+            const int x1 = ct[0] + (int)fminf(fmaxf(floorf(fr[0] + h), -kFarBuckets), kFarBuckets);
             if (ok) {
                 beg[u] = cs[at + min(max(x0, 0), gp.n[0] - 1)];
                 end[u] = cs[at + min(max(x1, 0), gp.n[0] - 1) + 1];

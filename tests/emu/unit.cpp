@@ -2,6 +2,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <sys/mman.h>
 
 #include "fit.h"
 
@@ -40,9 +41,37 @@ static void words()
     check(most <= kMaxWords && (kMaxWords | 1) * 64 * 4 == 67840, "64 targets in 67,840 bytes");
 }
 
+// A ball over all of 2^30 buckets, the most a grid has, reaches the last one
+// (offsets of untouched pages: zero).
+static void most_buckets()
+{
+    const int n = 1 << 30;
+    const size_t bytes = sizeof(int) * ((size_t)n + 1);
+    void *m = mmap(nullptr, bytes, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE,
+                   -1, 0);
+    check(m != MAP_FAILED, "mmap");
+    int *cs = (int *)m;
+    cs[n] = 9;
+    GridParams gp{};
+    gp.dim = gp.sub = 1;
+    gp.n[0] = gp.n_cells = n;
+    gp.stride[0] = 1;
+    gp.hi[0] = n;
+    gp.w[0] = gp.inv_w[0] = gp.g[0] = gp.wm = 1.0;
+    for (double at : {0.5, 1e9, (double)n - 0.5, 3.0 * n, -2.0 * n}) {
+        const double t[1] = {at};
+        RowLines<1, false> it(gp, cs, t, 16.0 * n * (double)n);
+        int beg[kRows], end[kRows];
+        check(it.next(beg, end) && beg[0] == 0 && end[0] == 9, "the ball's range ends at the last bucket");
+        check(!it.next(beg, end), "one row");
+    }
+    munmap(m, bytes);
+}
+
 int main()
 {
     words();
+    most_buckets();
     std::puts("ok");
     return 0;
 }
