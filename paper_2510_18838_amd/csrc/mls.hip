@@ -107,8 +107,18 @@ int target_stride(const LaunchSpec &ls) { return lane_words(ls) | 1; }
 // * there are few targets: kernel times with one lane and with four: 2-D linear,
 //   1.5k targets, 76 and 37 us; 3-D linear, 15k targets, 118 and 62 us; 3-D
 //   linear, 30k targets among 3M sources, 376 and 215 us; 3-D quadratic, 500k
-//   targets, 733 and 967 us.  The line is one wave of quads for each of
-//   3 x 1024 SIMD slots.
+//   targets, 733 and 967 us.  The line is one wave of quads for each of the
+//   SIMD slots that the kernel's registers leave: 3 x 1024, and 2 x 1024 for the
+//   quadratic bases in 4-D and 5-D.  Calls in us with one lane and with four,
+//   kNN on a kept grid of 200k sources: linear, 49k targets, 3-D 296 and 265,
+//   5-D 1785 and 1390; 3-D quadratic, 16k targets 293 and 256, 49k 305 and 293,
+//   MIXED_REFINE 322 and 320; 4-D quadratic MIXED_REFINE, 32k targets 708 and
+//   562, 49k 691 and 746; 5-D 2016 and 1840, 2196 and 2550; MIXED, 4-D 685 and
+//   551, 674 and 719; 5-D 2038 and 2084, 2238 and 3041.  The FP64 kernels of
+//   those bases spill 2 KB per lane, which four lanes do four times, so
+//   their line is one wave of quads per CU: 4-D, 4k targets 681 and 581, 8k 713
+//   and 698, 16k 714 and 802, 32k 814 and 1335; 5-D, 2766 and 2193, 2841 and
+//   3136, 2949 and 3563, 3926 and 6401.
 // * or long lists leave few one-lane waves per CU, the fit is small, and the
 //   radius is not a k-th distance (whose window walks share badly).  Calls in
 //   us with one lane and with four, growing radius: 5-D linear FP64, 1M
@@ -122,12 +132,19 @@ int target_stride(const LaunchSpec &ls) { return lane_words(ls) | 1; }
 //   4-D 613 and 563, 5-D 938 and 817; k_cap 32 420 and 426 (3-D).  k-th
 //   distances: k 85 (6 waves) 1016 and 743 (2-D), 1347 and 1039 (3-D), 4151
 //   and 3664 (5-D); k 64 (8 waves) 1681 and 1673 (4-D), 2496 and 2564 (5-D).
-constexpr int64_t kQuadTargets = 49152;
+constexpr int kCus = 256, kQuadsPerWave = 64 / kQuad;
 constexpr int kListsAlone = -1;   // for a degree
-int target_lanes(const LaunchSpec &ls, int degree)
+int64_t quad_targets(int dim, int degree, int precision)
+{
+    if (dim < 4 || degree < 2) return 3 * 4 * kCus * kQuadsPerWave;
+    return (precision == PCMS_FP64 ? 1 : 2 * 4) * kCus * kQuadsPerWave;
+}
+int target_lanes(const LaunchSpec &ls, int degree, int precision)
 {
     if (ls.grid->lbvh) return 1;
-    if (ls.n_tgt <= kQuadTargets) return kQuad;
+    // (a launch has fewer than 2^32 threads)
+    if (ls.n_tgt > ((int64_t)1 << 29)) return 1;
+    if (ls.n_tgt <= quad_targets(ls.grid->dim, degree, precision)) return kQuad;
     const int waves = (160 << 10) / (64 * target_stride(ls) * (int)sizeof(int));
     const bool knn = ls.radius.mode == PCMS_RADIUS_KNN;
     if (degree == kListsAlone) return waves <= (knn ? 6 : 9) ? kQuad : 1;
@@ -195,7 +212,7 @@ pcms_status launch_neighbors(const LaunchSpec &ls, int32_t *nbr, int32_t *n_kept
                              int32_t *n_found, double *r2, uint8_t *status, hipStream_t s)
 {
     if (ls.n_tgt == 0) return PCMS_OK;
-    const int lanes = target_lanes(ls, kListsAlone);
+    const int lanes = target_lanes(ls, kListsAlone, PCMS_FP64);
     const int block = pick_block(ls.block, ls, lanes);
     KArgs a = base_args(ls, block, lanes);
     a.nbr = nbr;
@@ -216,7 +233,7 @@ pcms_status launch_transfer(const LaunchSpec &ls, const double *svals, int n_fie
                             double *stage, uint8_t *status, hipStream_t s)
 {
     if (ls.n_tgt == 0) return PCMS_OK;
-    const int lanes = target_lanes(ls, degree);
+    const int lanes = target_lanes(ls, degree, precision);
     const int block = pick_block(ls.block, ls, lanes);
     KArgs a = base_args(ls, block, lanes);
     a.svals = svals;
@@ -241,7 +258,7 @@ pcms_status launch_operator(const LaunchSpec &ls, int degree, int weight, int pr
                             uint8_t *status, hipStream_t s)
 {
     if (ls.n_tgt == 0) return PCMS_OK;
-    const int lanes = target_lanes(ls, degree);
+    const int lanes = target_lanes(ls, degree, precision);
     const int block = pick_block(ls.block, ls, lanes);
     KArgs a = base_args(ls, block, lanes);
     a.weight = weight;
