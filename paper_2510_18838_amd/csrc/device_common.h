@@ -285,14 +285,15 @@ PCMS_HD PCMS_INLINE void load_src(const double *__restrict__ spts, int p, double
 // Sorted sources also keep an FP32 image of their coordinates relative to
 // the grid origin, fl32(s_k - lo_k), packed with no padding (a 3-D point is
 // 12 bytes and loads as one 12-byte word: ten records share a 128-byte line
-// instead of eight); the mixed-precision searches classify candidates from it.
-PCMS_HD PCMS_INLINE constexpr int padded_dim32(int d) { return d; }
+// instead of eight); the searches classify candidates from it.
 
 // Floats of storage after the FP32 and fixed-point records, which a walk's
 // whole-word loads may read past the last record.
 constexpr int kPad32 = 16;
 #ifndef PCMS_HOST_EMULATION
 typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
+#else
+typedef float float4u __attribute__((vector_size(16), aligned(4), may_alias));
 #endif
 
 // Square root to within 2^-22 (one instruction on the GPU).
@@ -491,7 +492,21 @@ struct Grp<1> {
 };
 #endif
 
-// --- pieces of the stable radix-sort scatter (one 8-bit digit per pass) ------
+// --- pieces of the stable radix sort (one 8-bit digit per pass) ---------------
+constexpr int kSortThreads = 256;          // 4 waves of 64
+constexpr int kSortRounds = 16;            // keys per thread of a block
+constexpr int kSortItems = kSortThreads * kSortRounds;
+// Blocks up to which a scatter sums the other blocks' counts itself: one launch
+// less per pass, for 256 nb more reads per block.
+constexpr int kDirectBlocks = 32;
+
+// Slot in its block of thread t's key of round r: each wave has a quarter of the
+// block's keys, 64 a round.
+PCMS_HD PCMS_INLINE int sort_slot(int t, int r)
+{
+    return (t >> 6) * (kSortItems / 4) + r * 64 + (t & 63);
+}
+
 // Lanes of one wave holding the same digit: AND of the per-bit ballots.
 PCMS_HD PCMS_INLINE unsigned long long digit_match(unsigned long long valid,
                                                    const unsigned long long (&bits)[8], int digit)
@@ -506,14 +521,36 @@ PCMS_HD PCMS_INLINE unsigned long long lanes_below(int lane)
     return lane == 0 ? 0ull : ((~0ull) >> (64 - lane));
 }
 
-// Output slot of an item: block running offset of its digit, plus the items
-// of the same digit in earlier waves of this round, plus earlier lanes.
-PCMS_HD PCMS_INLINE int scatter_slot(int running, const int (&wave_cnt)[4][256], int w, int digit,
-                                     unsigned long long mask, int lane)
+// The waves' counts of a digit become their offsets in the digit's run; returns
+// the run's length.
+PCMS_HD PCMS_INLINE int wave_offsets(int (&cnt)[4][256], int digit)
 {
-    int pos = running + __builtin_popcountll(mask & lanes_below(lane));
-    for (int v = 0; v < w; ++v) pos += wave_cnt[v][digit];
-    return pos;
+    int run = 0;
+    for (int v = 0; v < 4; ++v) {
+        const int c = cnt[v][digit];
+        cnt[v][digit] = run;
+        run += c;
+    }
+    return run;
+}
+
+// A digit's keys in all nb blocks and in those before block b, from its row of
+// the blocks' counts (DIRECT) or of their inclusive sums.
+template <bool DIRECT>
+PCMS_HD PCMS_INLINE void digit_counts(const int *row, int nb, int b, int &total, int &before)
+{
+    before = 0;
+    if (DIRECT) {
+        total = 0;
+        for (int x = 0; x < nb; ++x) {
+            const int c = row[x];
+            before += x < b ? c : 0;
+            total += c;
+        }
+    } else {
+        total = row[nb - 1];
+        if (b > 0) before = row[b - 1];
+    }
 }
 
 }  // namespace pcms

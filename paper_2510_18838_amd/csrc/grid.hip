@@ -18,9 +18,6 @@ namespace pcms {
 
 namespace {
 
-constexpr int kSortThreads = 256;          // 4 waves of 64
-constexpr int kSortRounds = 16;            // items per thread per block
-constexpr int kSortItems = kSortThreads * kSortRounds;
 constexpr int kScanThreads = 256;
 constexpr int kScanItems = 4 * kScanThreads;
 
@@ -245,17 +242,16 @@ __device__ __forceinline__ int scan_digits(int c, int *s)
     return s[t] - c;
 }
 
-// Ranks of a wave's keys (slot first + 64 r, r < kSortRounds; valid below n)
-// among the earlier ones of their digit, the digits' counts left in cnt: the
+// Ranks of a wave's keys (at base + sort_slot, valid below n) among the earlier ones of their digit, the digits' counts left in cnt: the
 // wave's running count of the digit plus the earlier lanes of the round (wave
 // multisplit).
-__device__ __forceinline__ void wave_ranks(const unsigned (&key)[kSortRounds], int first, int n,
+__device__ __forceinline__ void wave_ranks(const unsigned (&key)[kSortRounds], int base, int n,
                                            int shift, int *cnt, int (&pos)[kSortRounds])
 {
     const int lane = threadIdx.x & 63;
 #pragma unroll
     for (int r = 0; r < kSortRounds; ++r) {
-        const bool valid = first + r * 64 < n;
+        const bool valid = base + sort_slot(threadIdx.x, r) < n;
         const int digit = (key[r] >> shift) & 255;
         unsigned long long bits[8];
 #pragma unroll
@@ -280,12 +276,11 @@ k_sort_block(unsigned *__restrict__ keys, int *__restrict__ vals, int n, int shi
     __shared__ unsigned skey[kSortItems];
     __shared__ int sval[kSortItems];
     const int t = threadIdx.x, w = t >> 6;
-    const int first = w * (kSortItems / 4) + (t & 63);
     unsigned key_r[kSortRounds];
     int val_r[kSortRounds], pos_r[kSortRounds];
 #pragma unroll
     for (int r = 0; r < kSortRounds; ++r) {
-        const int i = first + r * 64;
+        const int i = sort_slot(t, r);
         key_r[r] = i < n ? keys[i] : 0u;
         val_r[r] = i < n ? vals[i] : 0;
     }
@@ -293,20 +288,13 @@ k_sort_block(unsigned *__restrict__ keys, int *__restrict__ vals, int n, int shi
 #pragma unroll
         for (int v = 0; v < 4; ++v) cnt[v][t] = 0;
         __syncthreads();
-        wave_ranks(key_r, first, n, shift, cnt[w], pos_r);
+        wave_ranks(key_r, 0, n, shift, cnt[w], pos_r);
         __syncthreads();
-        int run = 0;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int c = cnt[v][t];
-            cnt[v][t] = run;
-            run += c;
-        }
-        lstart[t] = scan_digits(run, scan);
+        lstart[t] = scan_digits(wave_offsets(cnt, t), scan);
         __syncthreads();
 #pragma unroll
         for (int r = 0; r < kSortRounds; ++r) {
-            if (first + r * 64 < n) {
+            if (sort_slot(t, r) < n) {
                 const int digit = (key_r[r] >> shift) & 255;
                 const int p = lstart[digit] + cnt[w][digit] + pos_r[r];
                 skey[p] = key_r[r];
@@ -316,7 +304,7 @@ k_sort_block(unsigned *__restrict__ keys, int *__restrict__ vals, int n, int shi
         __syncthreads();
 #pragma unroll
         for (int r = 0; r < kSortRounds; ++r) {
-            const int i = first + r * 64;
+            const int i = sort_slot(t, r);
             if (i < n) {
                 key_r[r] = skey[i];
                 val_r[r] = sval[i];
@@ -325,7 +313,7 @@ k_sort_block(unsigned *__restrict__ keys, int *__restrict__ vals, int n, int shi
     }
 #pragma unroll
     for (int r = 0; r < kSortRounds; ++r) {
-        const int i = first + r * 64;
+        const int i = sort_slot(t, r);
         if (i < n) {
             keys[i] = key_r[r];
             vals[i] = val_r[r];
@@ -358,49 +346,31 @@ k_digit_scatter(const unsigned *__restrict__ kin, const int *__restrict__ vin, i
     __shared__ int sval[kSortItems];
     const int t = threadIdx.x, w = t >> 6;
     const int base = blockIdx.x * kSortItems;
-    const int first = base + w * (kSortItems / 4) + (t & 63);
 #pragma unroll
     for (int v = 0; v < 4; ++v) cnt[v][t] = 0;
     unsigned key_r[kSortRounds];
     int val_r[kSortRounds], pos_r[kSortRounds];
 #pragma unroll
     for (int r = 0; r < kSortRounds; ++r) {
-        const int i = first + r * 64;
+        const int i = base + sort_slot(t, r);
         key_r[r] = i < n ? kin[i] : 0u;
         val_r[r] = i < n ? vin[i] : 0;
     }
     __syncthreads();
-    wave_ranks(key_r, first, n, shift, cnt[w], pos_r);
+    wave_ranks(key_r, base, n, shift, cnt[w], pos_r);
     __syncthreads();
     // digit t: the waves' offsets in its run, the run's start in the block,
     // and its global offset less that start
-    int run = 0;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        const int c = cnt[v][t];
-        cnt[v][t] = run;
-        run += c;
-    }
-    const int start = scan_digits(run, scan);
+    const int start = scan_digits(wave_offsets(cnt, t), scan);
     lstart[t] = start;
-    int total, before = 0;
-    if (DIRECT) {
-        total = 0;
-        for (int b = 0; b < nb; ++b) {
-            const int c = hist[t * nb + b];
-            before += b < (int)blockIdx.x ? c : 0;
-            total += c;
-        }
-    } else {
-        total = hist[t * nb + nb - 1];
-        if (blockIdx.x > 0) before = hist[t * nb + blockIdx.x - 1];
-    }
+    int total, before;
+    digit_counts<DIRECT>(hist + t * nb, nb, blockIdx.x, total, before);
     __syncthreads();
     gstart[t] = scan_digits(total, scan) + before - start;
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < kSortRounds; ++r) {
-        if (first + r * 64 < n) {
+        if (base + sort_slot(t, r) < n) {
             const int digit = (key_r[r] >> shift) & 255;
             const int p = lstart[digit] + cnt[w][digit] + pos_r[r];
             skey[p] = key_r[r];
@@ -485,10 +455,6 @@ int key_bits(int n_cells_cap)
     while (b < 31 && (1u << b) < (unsigned)n_cells_cap) ++b;
     return b;
 }
-
-// Blocks up to which a scatter sums the other blocks' counts itself: one
-// launch less per pass, for 256 nb more reads per block.
-constexpr int kDirectBlocks = 32;
 
 // Sorts (keys, vals) stably by key bits [lo_bit, bits); the result ends up
 // in (k0, v0).  One launch for one block's keys; else per pass a histogram, a

@@ -309,7 +309,6 @@ struct Image32 {
     template <int G, int B>
     PCMS_HD PCMS_INLINE void load(int p, int end, int q, float (&s)[B][D]) const
     {
-#ifndef PCMS_HOST_EMULATION
         if constexpr (G == 1) {
             static_assert(B * D % 4 == 0 && (B - 1) * D <= kPad32, "whole 16-byte words");
             const float4u *b = reinterpret_cast<const float4u *>(s32 + (size_t)p * D);
@@ -324,13 +323,12 @@ struct Image32 {
             for (int j = 0; j < B; ++j)
 #pragma unroll
                 for (int k = 0; k < D; ++k) s[j][k] = x[j * D + k];
-            return;
-        }
-#endif
+        } else {
 #pragma unroll
-        for (int j = 0; j < B; ++j) {
-            const int x = p + j * G + q;
-            load_src32<D>(s32, x < end ? x : p, s[j]);
+            for (int j = 0; j < B; ++j) {
+                const int x = p + j * G + q;
+                load_src32<D>(s32, x < end ? x : p, s[j]);
+            }
         }
     }
     PCMS_HD PCMS_INLINE float d2(const float (&s)[D]) const

@@ -102,72 +102,95 @@ struct Reader {
     }
 };
 
-constexpr int kSortThreads = 256, kSortRounds = 16, kSortItems = kSortThreads * kSortRounds;
+// One block's ranking (wave_ranks): pos[slot] is a key's rank among its digit's
+// earlier ones in its wave's quarter, cnt[w][d] the quarter's keys of digit d.
+void rank_block(const std::vector<unsigned> &keys, int base, int n, int shift, int (&cnt)[4][256],
+                std::vector<int> &pos)
+{
+    std::memset(cnt, 0, sizeof(cnt));
+    for (int w = 0; w < 4; ++w)
+        for (int r = 0; r < kSortRounds; ++r) {
+            unsigned long long valid = 0, bits[8] = {}, mask[64];
+            int digit[64], slot[64];
+            for (int lane = 0; lane < 64; ++lane) {
+                slot[lane] = sort_slot(64 * w + lane, r);
+                const int i = base + slot[lane];
+                digit[lane] = ((i < n ? keys[i] : 0u) >> shift) & 255;
+                if (i < n) valid |= 1ull << lane;
+                for (int b = 0; b < 8; ++b)
+                    if ((digit[lane] >> b) & 1) bits[b] |= 1ull << lane;
+            }
+            // every lane reads the count before a digit's first lane raises it
+            for (int lane = 0; lane < 64; ++lane) {
+                mask[lane] = digit_match(valid, bits, digit[lane]);
+                pos[slot[lane]] = cnt[w][digit[lane]] +
+                                  __builtin_popcountll(mask[lane] & lanes_below(lane));
+            }
+            for (int lane = 0; lane < 64; ++lane)
+                if (((valid >> lane) & 1) && (mask[lane] & lanes_below(lane)) == 0)
+                    cnt[w][digit[lane]] += __builtin_popcountll(mask[lane]);
+        }
+}
 
-// Stable LSD radix sort with the kernels' structure: per-block digit
-// histograms (digit-major), exclusive scan, then per-block rounds of 256
-// items in 4 waves, ranked with the ballot pieces the kernel uses.
-void radix_sort_emu(std::vector<unsigned> &keys, std::vector<int> &vals, int bits)
+// Stable LSD radix sort by key bits [lo_bit, bits) with the kernels' structure:
+// all passes in one block for one block's keys (k_sort_block); else per pass the
+// blocks' digit counts (k_digit_hist), their inclusive sums for more than
+// kDirectBlocks blocks (k_digit_scan), and a scatter that places a block's keys
+// digit-sorted before it writes them (k_digit_scatter).
+void radix_sort_emu(std::vector<unsigned> &keys, std::vector<int> &vals, int bits, int lo_bit = 0)
 {
     const int n = (int)keys.size();
     const int nb = (n + kSortItems - 1) / kSortItems;
+    if (nb == 0) return;
+    const int passes = std::max(1, (bits - lo_bit + 7) / 8);
+    std::fprintf(stderr, "sort: %d keys, %s\n", n,
+                 nb == 1 ? "one block" : nb <= kDirectBlocks ? "direct" : "scanned");
     std::vector<unsigned> kout(n);
-    std::vector<int> vout(n);
-    const int passes = std::max(1, (bits + 7) / 8);
+    std::vector<int> vout(n), pos(kSortItems);
     for (int ps = 0; ps < passes; ++ps) {
-        const int shift = 8 * ps;
+        const int shift = lo_bit + 8 * ps;
         std::vector<int> hist((size_t)256 * nb, 0);
-        for (int b = 0; b < nb; ++b)
-            for (int r = 0; r < kSortRounds; ++r)
-                for (int t = 0; t < kSortThreads; ++t) {
-                    int i = b * kSortItems + r * kSortThreads + t;
-                    if (i < n) hist[(size_t)((keys[i] >> shift) & 255) * nb + b]++;
-                }
-        int run = 0;
-        for (auto &h : hist) {
-            int c = h;
-            h = run;
-            run += c;
-        }
+        for (int i = 0; i < n; ++i) hist[(size_t)((keys[i] >> shift) & 255) * nb + i / kSortItems]++;
+        const bool scanned = nb > kDirectBlocks;
+        if (scanned)
+            for (int d = 0; d < 256; ++d)
+                for (int b = 1; b < nb; ++b) hist[(size_t)d * nb + b] += hist[(size_t)d * nb + b - 1];
         for (int b = 0; b < nb; ++b) {
-            int running[256];
-            for (int d = 0; d < 256; ++d) running[d] = hist[(size_t)d * nb + b];
-            for (int r = 0; r < kSortRounds; ++r) {
-                const int base = b * kSortItems + r * kSortThreads;
-                if (base >= n) break;
-                unsigned key[256];
-                int val[256], digit[256];
-                bool valid[256];
-                for (int t = 0; t < 256; ++t) {
-                    int i = base + t;
-                    valid[t] = i < n;
-                    key[t] = valid[t] ? keys[i] : 0u;
-                    val[t] = valid[t] ? vals[i] : 0;
-                    digit[t] = (key[t] >> shift) & 255;
+            const int base = b * kSortItems, in_block = std::min(kSortItems, n - base);
+            int cnt[4][256], lstart[256], gstart[256], run = 0, all = 0;
+            rank_block(keys, base, n, shift, cnt, pos);
+            for (int d = 0; d < 256; ++d) {
+                lstart[d] = run;
+                run += wave_offsets(cnt, d);
+                int total, before;
+                if (nb == 1) {          // k_sort_block keeps the block's own order
+                    total = 0;
+                    before = lstart[d];
+                    all = 0;
+                } else if (scanned) {
+                    digit_counts<false>(&hist[(size_t)d * nb], nb, b, total, before);
+                } else {
+                    digit_counts<true>(&hist[(size_t)d * nb], nb, b, total, before);
                 }
-                unsigned long long vb[4] = {0, 0, 0, 0}, bb[4][8] = {};
-                for (int t = 0; t < 256; ++t) {
-                    int w = t >> 6, lane = t & 63;
-                    if (valid[t]) vb[w] |= 1ull << lane;
-                    for (int q = 0; q < 8; ++q)
-                        if ((digit[t] >> q) & 1) bb[w][q] |= 1ull << lane;
+                gstart[d] = all + before - lstart[d];
+                all += total;
+            }
+            if (run != in_block) die("radix sort: a block's counts are not its keys");
+            std::vector<int> at(in_block, -1);   // block slot -> its key
+            for (int t = 0; t < kSortThreads; ++t)
+                for (int r = 0; r < kSortRounds; ++r) {
+                    const int j = sort_slot(t, r), i = base + j;
+                    if (i >= n) continue;
+                    const int d = (keys[i] >> shift) & 255;
+                    const int p = lstart[d] + cnt[t >> 6][d] + pos[j];
+                    if (p < 0 || p >= in_block || at[p] >= 0) die("radix sort: block slot taken twice");
+                    at[p] = i;
                 }
-                unsigned long long mask[256];
-                int wave_cnt[4][256];
-                std::memset(wave_cnt, 0, sizeof(wave_cnt));
-                for (int t = 0; t < 256; ++t) mask[t] = digit_match(vb[t >> 6], bb[t >> 6], digit[t]);
-                for (int t = 0; t < 256; ++t)
-                    if (valid[t] && (mask[t] & lanes_below(t & 63)) == 0)
-                        wave_cnt[t >> 6][digit[t]] = __builtin_popcountll(mask[t]);
-                for (int t = 0; t < 256; ++t) {
-                    if (!valid[t]) continue;
-                    int pos = scatter_slot(running[digit[t]], wave_cnt, t >> 6, digit[t], mask[t], t & 63);
-                    if (pos < 0 || pos >= n) die("radix scatter slot out of range");
-                    kout[pos] = key[t];
-                    vout[pos] = val[t];
-                }
-                for (int d = 0; d < 256; ++d)
-                    running[d] += wave_cnt[0][d] + wave_cnt[1][d] + wave_cnt[2][d] + wave_cnt[3][d];
+            for (int j = 0; j < in_block; ++j) {
+                const int o = gstart[(keys[at[j]] >> shift) & 255] + j;
+                if (o < 0 || o >= n) die("radix sort: output slot out of range");
+                kout[o] = keys[at[j]];
+                vout[o] = vals[at[j]];
             }
         }
         keys.swap(kout);
@@ -286,14 +309,15 @@ int main(int argc, char **argv)
     std::vector<double> spts((size_t)(n_src * dp), 0.0);
     for (int64_t p = 0; p < n_src; ++p)
         for (int q = 0; q < dim; ++q) spts[p * dp + q] = src[(size_t)perm[p] * dim + q];
-    // FP32 records as the gather kernel writes them
-    const int dp32 = padded_dim32(dim);
-    std::vector<float> spts32((size_t)(n_src * dp32), 0.0f);
+    // FP32 records as the gather kernel writes them, the fixed-point records and
+    // the pad behind them (one allocation, as in the library: the walks' whole
+    // words may read past the last FP32 record)
+    std::vector<uint32_t> recs((size_t)(2 * n_src * dim) + kPad32, 0u);
+    float *spts32 = reinterpret_cast<float *>(recs.data());
     for (int64_t p = 0; p < n_src; ++p)
         for (int q = 0; q < dim; ++q)
-            spts32[p * dp32 + q] = (float)(src[(size_t)perm[p] * dim + q] - gp.lo[q]);
-    // fixed-point records as the gather kernel writes them
-    std::vector<uint32_t> sq((size_t)(n_src * dim), 0u);
+            spts32[p * dim + q] = (float)(src[(size_t)perm[p] * dim + q] - gp.lo[q]);
+    uint32_t *sq = recs.data() + n_src * dim;
     for (int64_t p = 0; p < n_src; ++p)
         for (int q = 0; q < dim; ++q)
             sq[p * dim + q] = quantize(src[(size_t)perm[p] * dim + q], gp.lo[q], gp.iqs[q]);
@@ -338,11 +362,7 @@ int main(int argc, char **argv)
         }
     }
     // the library sorts on the key's top 24 bits only
-    if (tbits > 24) {
-        for (auto &k : tkeys) k >>= (tbits - 24);
-        tbits = 24;
-    }
-    radix_sort_emu(tkeys, tperm, tbits);
+    radix_sort_emu(tkeys, tperm, tbits, std::max(tbits - 24, 0));
     const int nfs = padded_dim((int)nf);
     std::vector<double> svals((size_t)(n_src * nfs), 0.0);
     for (int64_t p = 0; p < n_src; ++p)
@@ -352,8 +372,8 @@ int main(int argc, char **argv)
     a.gp = &gp;
     a.cs = cs.data();
     a.spts = spts.data();
-    a.spts32 = spts32.data();
-    a.sq = sq.data();
+    a.spts32 = spts32;
+    a.sq = sq;
     a.bvh_nodes = lbvh ? nodes : nullptr;
     if (lbvh) std::fprintf(stderr, "lbvh: %d leaves over %lld sources\n", n_leaves, (long long)n_src);
     a.perm = perm.data();
