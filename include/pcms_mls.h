@@ -272,7 +272,8 @@ int32_t pcms_operator_width(const pcms_operator *op);
 /* Release the operator (waits for its device first, whichever is current).
  * If that fails (PCMS_ERR_HIP), the operator is still there and can be released
  * again.  Up to 1 GiB per device of released operators' memory is kept for the
- * next pcms_operator_build. */
+ * next pcms_operator_build, and given back to the device when an allocation of
+ * the library on it finds no memory. */
 pcms_status pcms_operator_free(pcms_operator *op);
 
 /* ---------------------------------------------------------------------- */

@@ -272,34 +272,14 @@ pcms_status hip_fail(hipError_t e, const char *what)
     return e == hipErrorOutOfMemory ? PCMS_ERR_NOMEM : PCMS_ERR_HIP;
 }
 
-pcms_status scratch_alloc(void **p, size_t bytes, hipStream_t s)
-{
-    int dev = 0;
-    PCMS_HIP(hipGetDevice(&dev));
-    if (dev >= 0 && dev < 64) {
-        std::call_once(g_pool_once[dev], [dev]() {
-            hipMemPool_t pool;
-            if (hipDeviceGetDefaultMemPool(&pool, dev) == hipSuccess) {
-                uint64_t keep = UINT64_MAX;   // keep freed blocks cached in the pool
-                (void)hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &keep);
-            }
-        });
-    }
-    hipError_t e = hipMallocAsync(p, bytes > 0 ? bytes : 256, s);
-    if (e != hipSuccess) return hip_fail(e, "hipMallocAsync");
-    return PCMS_OK;
-}
-
-void scratch_free(void *p, hipStream_t s)
-{
-    if (p) (void)hipFreeAsync(p, s);
-}
-
 namespace {
 // Operators' arrays (0.5 GB for 1M targets of 48 slots) come from a pool of
 // their own per device, which keeps up to kOperatorKeep bytes of released ones
-// for the next build: hipMalloc and hipFree of such a block took 15 of the 19
-// ms of a build, apply and free of that size.
+// for the next build: hipMalloc and hipFree of such a block took 7 to 15 of the
+// 9 to 19 ms of a build, apply and free of that size, as the allocator's state
+// was.  1 GiB keeps operators of up to 1.8M targets of 48 slots; a larger one is
+// given back when it is released and pays for its memory each time.  Where an
+// allocation of the library finds no memory, the pool gives back what it holds.
 constexpr size_t kOperatorKeep = (size_t)1 << 30;
 constexpr int kPoolDevices = 64;
 std::mutex g_op_mu;
@@ -325,6 +305,59 @@ pcms_status operator_pool(int dev, hipMemPool_t *out)
     return PCMS_OK;
 }
 
+// Gives what the current device's operator pool holds unused back to the device;
+// false if there is no pool.
+bool operator_pool_release()
+{
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kPoolDevices) return false;
+    std::lock_guard<std::mutex> lock(g_op_mu);
+    return g_op_pool[dev] && hipMemPoolTrimTo(g_op_pool[dev], 0) == hipSuccess;
+}
+
+// An allocation, repeated once where it found no memory and the pool may have
+// held some.
+template <class F>
+hipError_t alloc_or_release(F &&alloc)
+{
+    hipError_t e = alloc();
+    if (e == hipErrorOutOfMemory && operator_pool_release()) {
+        (void)hipGetLastError();
+        e = alloc();
+    }
+    return e;
+}
+}  // namespace
+
+hipError_t device_alloc(void **p, size_t bytes)
+{
+    return alloc_or_release([&]() { return hipMalloc(p, bytes); });
+}
+
+pcms_status scratch_alloc(void **p, size_t bytes, hipStream_t s)
+{
+    int dev = 0;
+    PCMS_HIP(hipGetDevice(&dev));
+    if (dev >= 0 && dev < 64) {
+        std::call_once(g_pool_once[dev], [dev]() {
+            hipMemPool_t pool;
+            if (hipDeviceGetDefaultMemPool(&pool, dev) == hipSuccess) {
+                uint64_t keep = UINT64_MAX;   // keep freed blocks cached in the pool
+                (void)hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &keep);
+            }
+        });
+    }
+    hipError_t e = alloc_or_release([&]() { return hipMallocAsync(p, bytes > 0 ? bytes : 256, s); });
+    if (e != hipSuccess) return hip_fail(e, "hipMallocAsync");
+    return PCMS_OK;
+}
+
+void scratch_free(void *p, hipStream_t s)
+{
+    if (p) (void)hipFreeAsync(p, s);
+}
+
+namespace {
 // Gives an operator's block back to its device's pool, and what the pool holds
 // beyond kOperatorKeep to the device.  Work on any stream of the device may
 // still read the block, and giving it back waits for none of it, so the
@@ -597,13 +630,13 @@ static pcms_status grid_create(int64_t n_src, int32_t dim, const double *inv_sca
     for (int k = 0; k < kMaxDim; ++k) g->g[k] = (inv_scale && k < dim) ? inv_scale[k] : 1.0;
     hipError_t e;
     if ((e = hipGetDevice(&g->device)) != hipSuccess ||
-        (e = hipMalloc(&g->params, sizeof(GridParams))) != hipSuccess ||
-        (e = hipMalloc(&g->cell_start, sizeof(int) * ((size_t)g->n_cells_cap + 1))) != hipSuccess ||
-        (e = hipMalloc(&g->perm, sizeof(int) * (size_t)n_src)) != hipSuccess ||
-        (e = hipMalloc(&g->iperm, sizeof(int) * (size_t)n_src)) != hipSuccess ||
-        (e = hipMalloc(&g->spts, sizeof(double) * (size_t)n_src * padded_dim(dim))) != hipSuccess ||
-        (e = hipMalloc(&g->spts32, sizeof(float) * (2 * (size_t)n_src * dim + kPad32))) != hipSuccess ||
-        (lbvh && (e = hipMalloc(&g->bvh_nodes, bvh_node_bytes(n_src, dim))) != hipSuccess)) {
+        (e = device_alloc((void **)&g->params, sizeof(GridParams))) != hipSuccess ||
+        (e = device_alloc((void **)&g->cell_start, sizeof(int) * ((size_t)g->n_cells_cap + 1))) != hipSuccess ||
+        (e = device_alloc((void **)&g->perm, sizeof(int) * (size_t)n_src)) != hipSuccess ||
+        (e = device_alloc((void **)&g->iperm, sizeof(int) * (size_t)n_src)) != hipSuccess ||
+        (e = device_alloc((void **)&g->spts, sizeof(double) * (size_t)n_src * padded_dim(dim))) != hipSuccess ||
+        (e = device_alloc((void **)&g->spts32, sizeof(float) * (2 * (size_t)n_src * dim + kPad32))) != hipSuccess ||
+        (lbvh && (e = device_alloc((void **)&g->bvh_nodes, bvh_node_bytes(n_src, dim))) != hipSuccess)) {
         grid_alloc_free(g);
         return hip_fail(e, "hipMalloc(grid)");
     }
@@ -856,7 +889,7 @@ pcms_status pcms_operator_build(const double *src, int64_t n_src, int32_t dim, c
     hipMemPool_t pool;
     op->device = g.device;
     if ((st = operator_pool(op->device, &pool)) != PCMS_OK) return st;
-    hipError_t he = hipMallocFromPoolAsync(&op->mem, bytes, pool, s);
+    hipError_t he = alloc_or_release([&]() { return hipMallocFromPoolAsync(&op->mem, bytes, pool, s); });
     if (he != hipSuccess) {
         op->mem = nullptr;
         return hip_fail(he, "hipMallocFromPoolAsync(operator)");

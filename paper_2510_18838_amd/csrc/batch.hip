@@ -409,7 +409,7 @@ pcms_status batch_setup(BatchPlan &p)
     const size_t o_s32 = take(sizeof(float) * (2 * s32 + kPad32));   // FP32 records, then fixed-point ones
     const size_t o_items = take(sizeof(int4) * std::max<size_t>(sorted.size(), 1));
     const size_t o_sum = take(sizeof(int32_t) * 4);
-    hipError_t e = hipMalloc(&p.ws, off);
+    hipError_t e = device_alloc(&p.ws, off);
     if (e != hipSuccess) {
         p.ws = nullptr;
         return hip_fail(e, "hipMalloc(batch workspace)");

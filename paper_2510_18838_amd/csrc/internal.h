@@ -45,6 +45,11 @@ pcms_status hip_fail(hipError_t e, const char *what);
         if (e_ != hipSuccess) return ::pcms::hip_fail(e_, #call);   \
     } while (0)
 
+// device memory ----------------------------------------------------------------
+// hipMalloc, after giving back what released operators' memory is still held
+// where that is what is missing.
+hipError_t device_alloc(void **p, size_t bytes);
+
 // stream-ordered scratch allocation ------------------------------------------
 pcms_status scratch_alloc(void **p, size_t bytes, hipStream_t s);
 void scratch_free(void *p, hipStream_t s);

@@ -53,3 +53,41 @@ def test_a_failed_release_is_reported_and_can_be_repeated(fake, call):
     assert L.pcms_operator_free(op) == 0
     assert sum("hipFreeAsync" in c for c in log()) == 1, log()
     """)
+
+
+CALLS = {
+    "operator": ("hipMallocFromPoolAsync", "build()[1]"),
+    "grid": ("hipMalloc", """L.pcms_grid_build(PTR, i64(500), 2, None, C.c_double(0), C.c_double(0),
+                                               None, C.byref(P()))"""),
+    "transfer": ("hipMallocAsync", """L.pcms_mls_transfer(
+        PTR, i64(500), 2, PTR, 1, PTR, i64(400), 1, C.byref(Radius(1, 8, 0, 0, 0.0)), 16, None, None,
+        None, PTR, PTR)"""),
+}
+
+
+@pytest.mark.parametrize("call", list(CALLS))
+def test_a_call_without_memory_takes_back_what_the_pool_holds(fake, call):
+    """Memory kept for the next operator is given back to the device where an
+    allocation of the library would fail without it."""
+    name, code = CALLS[call]
+    fake_hip.run(fake, BUILD, f"""
+    op, code = build()
+    assert code == 0 and L.pcms_operator_free(op) == 0
+    fake.fake_clear()
+    fail("{name}", HIP_ERROR_MEMORY, 1)
+    assert {code} == 0, L.pcms_last_error()
+    calls = log()
+    asked = [i for i, c in enumerate(calls) if c.startswith("{name}@")]
+    assert "hipMemPoolTrimTo@0 0" in calls[asked[0]:asked[1]], calls
+    fake.fake_clear()
+    fail("{name}", HIP_ERROR_MEMORY)
+    assert {code} == 3, "PCMS_ERR_NOMEM"
+    """)
+
+
+def test_a_call_without_memory_and_without_a_pool_asks_once(fake):
+    fake_hip.run(fake, BUILD, f"""
+    fail("hipMalloc", HIP_ERROR_MEMORY)
+    assert {CALLS["grid"][1]} == 3
+    assert sum(c.startswith("hipMalloc@") for c in log()) == 1, log()
+    """)
