@@ -530,7 +530,9 @@ pcms_status transfer_on_grid(const Grid *g, const double *src_vals, int32_t n_fi
     int *tperm = (int *)((char *)ws + L.off_tperm);
     double *svals = (double *)((char *)ws + L.off_svals);
     // few targets write their fields directly: their scattered stores cost
-    // less than the launch that transposes staged records (6 us)
+    // less than the launch that transposes staged records (calls of 2k to 49k
+    // targets, 1 to 64 fields, 3-D linear: 0.97 to 1.00 of the staged ones'
+    // time; 100k targets, 8 fields 317.3 and 317.7 us, 64 fields 573.7 and 554.5)
     const bool direct = n_tgt <= kDirectTargets;
     double *stage = direct ? nullptr : (double *)((char *)ws + L.off_stage);
     if ((st = zero_ints(summary, 4, s)) != PCMS_OK) return st;

@@ -341,10 +341,11 @@ PCMS_HD PCMS_INLINE void load_srcq(const uint32_t *__restrict__ sq, int p, uint3
 PCMS_HD PCMS_INLINE float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 PCMS_HD PCMS_INLINE double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
-// Square root of x >= 0 in FP64: the reciprocal root's approximation, one
-// Goldschmidt step and two Newton corrections, as accurate as sqrt (the same
-// bits) for x from 1e-200 on; smaller ones, zero among them, give 1e-100.  It
-// leaves out the range scaling of sqrt, half of its instructions.
+// Square root of finite x >= 0 in FP64: the reciprocal root's approximation, one
+// Goldschmidt step and two Newton corrections (Markstein, "Software division and
+// square root using Goldschmidt's algorithms", RNC 6, 2004), as accurate as sqrt
+// (the same bits) for x from 1e-200 on; smaller ones, zero among them, give
+// 1e-100.  It leaves out the range scaling of sqrt, half of its instructions.
 PCMS_HD PCMS_INLINE double sqrt_unit(double x)
 {
 #if defined(__HIP_DEVICE_COMPILE__)

@@ -62,10 +62,12 @@ __global__ void __launch_bounds__(256) k_neighbors(KArgs a)
 // spill per lane under 168 VGPRs) and the 4-D and 5-D quadratic bases in
 // any precision (1-2 KB), which get two.  Measured with the row walks that
 // the row tables replaced: the 5-D linear MIXED_REFINE kernel went from 3-6 %
-// slower than FP64 to level with it (74.3 against 76.1 ms).  The
-// low-dimensional kernels need the third wave for latency even where they
-// spill a little: at two, the 3-D quadratic MIXED_REFINE kernel slowed from 7.0
-// to 9.2 ms and the 2-D quadratic one from 0.43 to 0.48 ms.
+// slower than FP64 to level with it (74.3 against 76.1 ms).  (With the tables
+// and four lanes, which need fewer registers, that kernel measures 26.0 ms with
+// two and 23.5 with three on 2M targets.)  The low-dimensional kernels need the
+// third wave for latency even where they spill a little: at two, the 3-D
+// quadratic MIXED_REFINE kernel slowed from 7.0 to 9.2 ms and the 2-D quadratic
+// one from 0.43 to 0.48 ms.
 template <int PREC, int D, int P>
 constexpr int waves_for()
 {

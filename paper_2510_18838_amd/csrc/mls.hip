@@ -111,7 +111,8 @@ int target_stride(const LaunchSpec &ls) { return lane_words(ls) | 1; }
 //   SIMD slots that the kernel's registers leave: 3 x 1024, and 2 x 1024 for the
 //   quadratic bases in 4-D and 5-D.  Calls in us with one lane and with four,
 //   kNN on a kept grid of 200k sources: linear, 49k targets, 3-D 296 and 265,
-//   5-D 1785 and 1390; 3-D quadratic, 16k targets 293 and 256, 49k 305 and 293,
+//   5-D 1785 and 1390, MIXED_REFINE 4-D 568 and 605 (growing radius 536 and
+//   423), 5-D 1811 and 1592; 3-D quadratic, 16k targets 293 and 256, 49k 305 and 293,
 //   MIXED_REFINE 322 and 320; 4-D quadratic MIXED_REFINE, 32k targets 708 and
 //   562, 49k 691 and 746; 5-D 2016 and 1840, 2196 and 2550; MIXED, 4-D 685 and
 //   551, 674 and 719; 5-D 2038 and 2084, 2238 and 3041.  The FP64 kernels of

@@ -38,7 +38,7 @@ __global__ void __launch_bounds__(256) k_op_apply(const int32_t *__restrict__ op
                                                   const double *__restrict__ svals, int nf, int nfs,
                                                   double *__restrict__ out, int n_blocks)
 {
-    // XCD-aware: each XCD takes a contiguous range of (spatially sorted)
+    // XCD-aware: each XCD takes chunks of consecutive (spatially sorted)
     // targets, so its L2 holds the records their neighbours share
     const int lb = logical_block(n_blocks);
     const int gi = lb * blockDim.x + threadIdx.x;
