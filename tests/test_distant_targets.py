@@ -12,7 +12,7 @@ from test_emulation import EmuBackend
 BACKENDS = {"one": EmuBackend(1), "four": EmuBackend(4), "tree": EmuBackend(1, lbvh=True)}
 
 
-def _problem(dim, box, far, mode):
+def problem(dim, box, far, mode):
     rng = np.random.default_rng([dim, int(-np.log10(box)), int(far), mode])
     n = 40
     # (a box of 1e-15 around 0.1 holds a few distinct coordinates)
@@ -29,5 +29,5 @@ def _problem(dim, box, far, mode):
                                          (3, 2e-12, 1000.0), (3, 1e-15, 1.0), (4, 1e-14, 30.0),
                                          (5, 1e-15, 1.0), (5, 3e-13, 500.0)])
 def test_lists(dim, box, far, mode, backend):
-    C.check_lists(BACKENDS[backend], _problem(dim, box, far, mode),
+    C.check_lists(BACKENDS[backend], problem(dim, box, far, mode),
                   f"{dim}-D box {box} far {far} mode {mode} ({backend})", brute=True)

@@ -17,11 +17,7 @@ SCALES = {"overflowing differences": (6e38, -3e38, 1e-38), "large and unit": (1e
           "subnormal coordinates": (2e-42, -1e-42, 1e37), "beyond the range": (1e60, 0.0, 1e-60)}
 
 
-@pytest.mark.parametrize("backend", list(BACKENDS))
-@pytest.mark.parametrize("mode", [synth.FIXED, synth.KNN, synth.GROW])
-@pytest.mark.parametrize("dim", [2, 3, 5])
-@pytest.mark.parametrize("kind", list(SCALES))
-def test_lists(kind, dim, mode, backend):
+def problem(kind, dim, mode):
     scale, offset, g = SCALES[kind]
     rng = np.random.default_rng([dim, mode, len(kind)])
     n = 1500
@@ -29,6 +25,14 @@ def test_lists(kind, dim, mode, backend):
     tgt = offset + scale * rng.uniform(-0.1, 1.1, (150, dim))
     tgt[:20] = src[:20]
     r = scale * g * (20 / (n * synth.unit_ball_volume(dim))) ** (1.0 / dim)
-    p = C.custom(src, rng.uniform(0.0, 1.0, (1, n)), tgt, 0, mode, k=16, radius=r, n_min=8,
-                 k_cap=24, inv_scale=[g] * dim)
-    C.check_lists(BACKENDS[backend], p, f"{kind} {dim}-D mode {mode} ({backend})", brute=True)
+    return C.custom(src, rng.uniform(0.0, 1.0, (1, n)), tgt, 0, mode, k=16, radius=r, n_min=8,
+                    k_cap=24, inv_scale=[g] * dim)
+
+
+@pytest.mark.parametrize("backend", list(BACKENDS))
+@pytest.mark.parametrize("mode", [synth.FIXED, synth.KNN, synth.GROW])
+@pytest.mark.parametrize("dim", [2, 3, 5])
+@pytest.mark.parametrize("kind", list(SCALES))
+def test_lists(kind, dim, mode, backend):
+    C.check_lists(BACKENDS[backend], problem(kind, dim, mode),
+                  f"{kind} {dim}-D mode {mode} ({backend})", brute=True)
